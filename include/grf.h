@@ -54,7 +54,7 @@ extern "C" {
 
 /* evaluation methods */
 #define GRF_AUTO (-1)       /* separable FP16 on grids with >= 2^16 cells, else DIRECT_F32 */
-#define GRF_DIRECT_F32 0    /* one cos per mode and cell, FP64 per-axis phase reduction */
+#define GRF_DIRECT_F32 0    /* FP32 sum of cosines (grids: cosine and sine products), phases reduced in FP64 */
 #define GRF_DIRECT_F64 1    /* FP64 throughout (small problems, reference-grade) */
 #define GRF_SEP_BF16 2      /* matrix-core contraction, bf16 tables, one pass */
 #define GRF_SEP_F16 3       /* matrix-core contraction, fp16 tables, one pass */
@@ -193,7 +193,8 @@ int eval_field_grid_ws_size(const grf_modes* modes, const grf_grid* grid, int me
  *                     At least one output must be non-NULL.  epi may be NULL when
  *                     k and ind are NULL.
  *   ws, ws_bytes      device workspace of eval_field_grid_ws_size bytes: the per-axis
- *                     tables; for DIRECT_F64 on grids too small to fill the device (under
+ *                     tables (DIRECT_F32 forms its operands on chip and leaves them
+ *                     unwritten); for DIRECT_F64 on grids too small to fill the device (under
  *                     131,072 cells) the FP64 partial sums of its mode slices; for the
  *                     separable methods on grids of fewer default tiles than the device
  *                     has CUs, the FP32 sums of the mode slices that the contraction is split

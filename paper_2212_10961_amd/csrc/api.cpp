@@ -280,6 +280,29 @@ int grid_table_descs(const grf_modes* m, const grf_grid* g, int method, const Gr
     return nd;
 }
 
+DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind)
+{
+    DirectGrid d{};
+    d.z = m->z;
+    d.phi = m->phi;
+    d.w = m->w;
+    for (int a = 0; a < 3; ++a) {
+        d.fs[a] = a < m->dim ? 1.0 / (6.283185307179586476925286766559 * m->ell[a]) : 0.0;
+        d.o[a] = a < m->dim ? g->origin[a] : 0.0;
+        d.h[a] = a < m->dim ? g->h[a] : 0.0;
+    }
+    d.ny = g->n[1];
+    d.nq = g->n[1] * g->n[2];
+    d.n = m->n;
+    d.nx = static_cast<int32_t>(g->n[0]);
+    d.dim = m->dim;
+    d.amp = static_cast<float>(m->sigma * std::sqrt(2.0 / static_cast<double>(m->n)));
+    d.y = y;
+    d.k = k;
+    d.ind = ind;
+    return d;
+}
+
 static hipError_t build_tables(const grf_modes* m, const grf_grid* g, int method, const GridWs& w,
                                hipStream_t s)
 {
@@ -372,9 +395,11 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
 {
     GridWs w = grid_ws(modes, grid, method, ws);
     if (!allow_split && w.split_bytes) w.partial = nullptr;  // the workspace holds the tables only
-    const float amp = static_cast<float>(modes->sigma * std::sqrt(2.0 / static_cast<double>(modes->n)));
-    const int64_t ldp = padded_modes(modes->n);
-
+    if (method == GRF_DIRECT_F32) {  // operands are formed on chip: no tables
+        TimedScope timed(s);
+        GRF_HIP(launch_direct_grid_f32(direct_grid_args(modes, grid, y, k, ind), e, s));
+        return GRF_OK;
+    }
     GRF_HIP(build_tables(modes, grid, method, w, s));
     if (is_sep(method)) {
         SepArgs a = sep_args(modes, grid, method, tile, e, y, k, ind, w);
@@ -383,16 +408,11 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
         return GRF_OK;
     }
     TimedScope timed(s);
-    if (method == GRF_DIRECT_F32) {
-        GRF_HIP(launch_direct_grid_f32(static_cast<const float*>(w.t[0]), static_cast<const float*>(w.t[1]),
-                                       static_cast<const float*>(w.t[2]), modes->w, modes->n, ldp, grid->n, amp, e,
-                                       y, k, ind, s));
-    } else if (method == GRF_DIRECT_F64) {
-        const double amp64 = modes->sigma * std::sqrt(2.0 / static_cast<double>(modes->n));
-        GRF_HIP(launch_direct_grid_f64(static_cast<const double*>(w.t[0]), static_cast<const double*>(w.t[1]),
-                                       static_cast<const double*>(w.t[2]), modes->w, modes->n, ldp, grid->n, amp64, e,
-                                       0.0, y, k, ind, nullptr, nullptr, static_cast<double*>(w.partial), s));
-    }
+    const double amp64 = modes->sigma * std::sqrt(2.0 / static_cast<double>(modes->n));
+    GRF_HIP(launch_direct_grid_f64(static_cast<const double*>(w.t[0]), static_cast<const double*>(w.t[1]),
+                                   static_cast<const double*>(w.t[2]), modes->w, modes->n, padded_modes(modes->n),
+                                   grid->n, amp64, e, 0.0, y, k, ind, nullptr, nullptr,
+                                   static_cast<double*>(w.partial), s));
     return GRF_OK;
 }
 

@@ -1,8 +1,8 @@
 // Batched ensembles of independent realisations on grids of uneven size.
 //
-// A plan turns a batch into three launches: a counter reset, one batched per-axis table
-// build over every instance (the FP64 range reduction), and one persistent kernel whose
-// blocks pull (instance, tile, slice) work items from an atomic counter.  The sequence is
+// A plan turns a batch into at most three launches: a counter reset, for the separable methods
+// one batched per-axis table build over every instance (the FP64 range reduction), and one
+// persistent kernel whose blocks pull (instance, tile, slice) work items from an atomic counter.  The sequence is
 // captured once in a hipGraph per batch signature and replayed afterwards.  For the
 // separable methods each instance's tile shape (128x128 or 64x64) comes from its size
 // class; with GRF_PLAN_AUTOTUNE the plan times both shapes on instances of each class the
@@ -228,7 +228,7 @@ static int build_plan(grf_plan* p, const grf_batch_item* items, int32_t n, hipSt
         toff[i] = tbytes;
         if (gen) {
             tbytes += align256(sizeof(uint32_t) * size_t(kGenRows) * size_t(ldp)) + align256(sizeof(GenMode) * size_t(ldp));
-        } else {
+        } else if (sep) {  // (the direct form makes its operands on chip from z and phi)
             ws[i] = grid_ws(&items[i].modes, &items[i].grid, p->method, nullptr);
             tbytes += ws[i].bytes - ws[i].split_bytes;  // tables only: batch tiles do not split the modes
         }
@@ -294,7 +294,7 @@ static int build_plan(grf_plan* p, const grf_batch_item* items, int32_t n, hipSt
         GRF_HIP(ensure(p->d_gmd, p->cap_gmd, gmd.size() * sizeof(GenModeDesc)));
         GRF_HIP(hipMemcpy(p->d_gmd, gmd.data(), gmd.size() * sizeof(GenModeDesc), hipMemcpyHostToDevice));
     }
-    if (!gen) {
+    if (sep && !gen) {
         int64_t total = 0;
         for (int32_t i = 0; i < n; ++i) {
             AxisTableArgs d[3];
@@ -349,23 +349,11 @@ static int build_plan(grf_plan* p, const grf_batch_item* items, int32_t n, hipSt
             const int32_t i = order[r];
             const grf_batch_item& it = items[i];
             DirectBatchItem& d = di[r];
-            d.tx = static_cast<const float*>(ws[i].t[0]);
-            d.ty = static_cast<const float*>(ws[i].t[1]);
-            d.tz = static_cast<const float*>(ws[i].t[2]);
-            d.w = it.modes.w;
-            d.y = it.y;
-            d.k = it.k;
-            d.ind = it.ind;
+            d.g = direct_grid_args(&it.modes, &it.grid, it.y, it.k, it.ind);
             d.epi = make_epi(&it.epi);
-            d.ldp = padded_modes(it.modes.n);
-            d.nq = it.grid.n[1] * it.grid.n[2];
-            d.n = static_cast<int32_t>(it.modes.n);
-            d.nx = static_cast<int32_t>(it.grid.n[0]);
-            d.ny = static_cast<int32_t>(it.grid.n[1]);
-            d.nxt = static_cast<int32_t>((it.grid.n[0] + kDirectTile - 1) / kDirectTile);
-            d.amp = static_cast<float>(it.modes.sigma * std::sqrt(2.0 / static_cast<double>(it.modes.n)));
+            d.tiles_i = (it.grid.n[0] + kDirectTile - 1) / kDirectTile;
             d.item0 = item;
-            item += static_cast<int64_t>(d.nxt) * ((d.nq + kDirectTile - 1) / kDirectTile);
+            item += d.tiles_i * ((d.g.nq + kDirectTile - 1) / kDirectTile);
         }
         p->total_items = item;
         GRF_HIP(ensure(p->d_items, p->cap_items, di.size() * sizeof(DirectBatchItem)));

@@ -2,12 +2,10 @@
 //   Y_c = A sum_j cos(2 pi r_jc),   r_jc = frac-reduced phase in revolutions,
 // plus the fused epilogue (K = exp(mu + Y), facies index = #{thresholds below Y}; Secs. 4.1
 // and 3.1).  At points: one hardware cosine per mode and point.  On grids the phase splits
-// into an x part and a (y,z) part, and each term is their angle sum, two FMAs on cosines
-// and sines formed once per grid row and mode.
+// into an x part and a (y,z) part, and the sum is a contraction of their cosines and sines on
+// the FP32 matrix cores.
 //
-// v_cos_f32 / v_sin_f32 take their argument in revolutions and reduce it exactly, so the
-// per-axis FP64-reduced fractions are summed in FP32 (values in [0, 3)) and fed to them
-// without a further reduction.
+// v_cos_f32 / v_sin_f32 take their argument in revolutions; phases are reduced in FP64 first.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,178 +25,208 @@ __device__ __forceinline__ void store_out(int64_t c, float yv, const Epi& e, flo
 }
 
 // ---------------------------------------------------------------------------- grid, FP32
-// Block tile: 16 RA x-cells by 16 RB (y,z) pairs; 256 threads; each lane owns RA x RB cells
-// (x = x0 + lx + 16 a, q = q0 + 4 RB w + (l / 16) + 4 b).  With the x phase A = 2 pi Tx and
-// the (y,z) phase B = 2 pi (Ty + Tz) (psi folded in Ty), each term is the angle sum
-// cos(A + B) = cos A cos B - sin A sin B: two FMAs.  Per chunk of J modes the block stages in
-// LDS, for each of its x rows, cos A and sin A (hardware cosine and sine of the FP64-reduced
-// fraction), and for each (y,z) row w cos B and w sin B (B from the FP32 sum of the two
-// fractions, w the mode weight, 1 without weights): rows [J cosines | J sines | 4 floats of
-// pad], so the 16 distinct x rows of a wave's 128-bit reads hit distinct banks.  Every cell
-// is summed by one lane over the modes in order, whatever the tile and chunk: neither changes
-// a result bit.  Large grids take 4 x 8 cells per lane (64 x 128 tiles, 32-mode chunks); the
-// batch and mid-size grids 4 x 4 (64 x 64); small grids 2 x 2 or 1 x 1 cells for more blocks,
-// with chunks of 64 or 256 modes so that the fewer terms per lane still cover each chunk's loads.
-constexpr int kDgB = 64;
-static_assert(kDgB == kDirectTile, "tile side shared with the batch planner");
+// The grid sum as a real contraction on the FP32 matrix cores.  Cell centres are symmetric about
+// the grid's middle along x: with x = xc + d the mirrored cell has offset -d, and with
+// B = a_x d, F = a_x xc + a_y y + a_z z + psi (in revolutions, formed and reduced in FP64)
+//   Y(+-d) = E -+ O,   E = sum_j w_j cos F cos B,   O = sum_j w_j sin F sin B,
+// so each pair of cells costs two multiply-adds per mode, half of the plain angle sum.  Both
+// sums are matrix products (rows the (y, z) pairs, columns the nx / 2 offsets, K the modes) of
+// FP32 operands with FP32 accumulation.
+//
+// A block is eight waves over one tile of TI TS rows x TS columns (2 TS cells along x).  Wave c
+// sums the modes of chunk c (an eighth of the table) and makes its operands in registers: lane l
+// owns rows l % TS and column l % TS and the mode j + l / TS of each step, two FP64 phases per
+// row tile and column and the hardware cosine and sine, the mode's z and phi broadcast from LDS
+// (staged 64 modes at a time, private to the wave).  No tables, no barrier in the mode loop.  The
+// eight chunk sums meet in LDS and are added in chunk order.  An FP32 matrix step rounds like
+// the FMAs of its k values in order (checked bit for bit), so the tile shape changes no result
+// bit: a grid and its batched evaluation agree exactly.
+//
+// What bounds it: 2 flops per mode and cell on the FP32 matrix cores (153 TFLOP/s in a library
+// product) plus the operands, about 41 issue cycles per cosine-sine pair: on gfx950 a vector
+// instruction does not issue beside another wave's FP32 matrix step (measured: the two add up),
+// so a 64-row tile's step of 4 x 64 matrix cycles costs ~380.  Making four steps' operands
+// together changed nothing.  The plain angle sum on the vector units (two FMAs per term on
+// tabulated phases) took, before -> after, one call: 128^3 x 4,096 modes 566 -> 174 us, a weighted
+// 517 x 301 x 2,048 table 120 -> 23 us, 64 x 64 x 1,000 27 -> 13 us; relative error against FP64
+// on 128^3 1.6e-6 -> 4.5e-7 (the phases are summed in FP64 and the chunks are shorter).
+constexpr int kDgWaves = 8;    // waves of a block = mode chunks of every sum
+constexpr int kDgStage = 64;   // modes staged in LDS per wave
+static_assert(kDirectTile == 64, "the batch tile is 64 rows x 32 columns (64 cells)");
 
 __device__ __forceinline__ float sin_rev(float r) { return __builtin_amdgcn_sinf(r); }
 
-// LDS float4 of one tile: 16 (RA + RB) rows of (2 J + 4) floats.
-template <int RA, int RB, int J>
-struct DirectShape {
-    static constexpr int ROW = (2 * J + 4) / 4;  // float4 per padded row
-    static constexpr int X4 = 16 * RA * ROW, Q4 = 16 * RB * ROW;
+typedef float dg_f16 __attribute__((ext_vector_type(16)));
+typedef float dg_f4 __attribute__((ext_vector_type(4)));
+
+template <int TS>
+struct DgTile;
+template <>
+struct DgTile<32> {
+    using Acc = dg_f16;
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int e, int l) { return 8 * (e >> 2) + 4 * (l >> 5) + (e & 3); }
+};
+template <>
+struct DgTile<16> {
+    using Acc = dg_f4;
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int e, int l) { return 4 * (l >> 4) + e; }
 };
 
-// One (16 RA) x (16 RB) (x, (y,z)) tile, mode chunks of J; `sx`, `sq` are LDS arrays of
-// DirectShape<RA, RB, J>::X4 and ::Q4 float4.  Whole block.
-template <int RA, int RB, int J>
-__device__ __forceinline__ void direct_tile(const float* __restrict__ tx, const float* __restrict__ ty,
-                                            const float* __restrict__ tz, const double* __restrict__ wt, int n,
-                                            int64_t ldp, int nx, int ny, int64_t nq, int x0, int64_t q0, float amp,
-                                            const Epi& epi, float* __restrict__ y, float* __restrict__ k,
-                                            uint8_t* __restrict__ ind, float4* sx, float4* sq)
+// LDS of one block: the waves' mode stages, later the chunk sums of one row tile.
+template <int TS>
+struct DgShape {
+    static constexpr int kModeB = kDgWaves * kDgStage * (4 * 8 + 4);
+    static constexpr int kSumB = kDgWaves * 2 * TS * TS * 4;
+    static constexpr int BYTES = kModeB > kSumB ? kModeB : kSumB;
+};
+
+// Rows q0 .. q0 + TI TS - 1, columns i0 .. i0 + TS - 1 (offsets from the middle; column i is cell
+// i and its mirror nx - 1 - i).  `smem`: DgShape<TS>::BYTES bytes, 16-byte aligned.  Whole block.
+template <int TS, int TI, bool WT>
+__device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi, int64_t i0, int64_t q0, char* smem)
 {
-    static_assert(J % 32 == 0, "row stride 2 J + 4 must be 4 (mod 64) floats");
-    const int t = threadIdx.x;
-    const int w = t >> 6, l = t & 63;
-    const int lx = l & 15, lq = w * 4 * RB + (l >> 4);
-    constexpr int kRow = DirectShape<RA, RB, J>::ROW;
-    constexpr int kG = J / 4;  // groups of 4 modes per chunk
+    using T = DgTile<TS>;
+    constexpr int KS = 64 / TS;         // modes per matrix step
+    constexpr int NE = TS * TS / 64;    // accumulator elements per lane
+    constexpr double kInvTwoPi = 0.15915494309189533576888376337251;
+    const int t = threadIdx.x, l = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int r = l % TS, kk = l / TS;
+    const int nx = g.nx, half = (nx + 1) >> 1;
+    const int64_t n = g.n;
 
-    float acc[RA][RB];
+    // coordinates times 1 / (2 pi ell): phases in revolutions are plain products with z
+    const int64_t ic = min(i0 + r, static_cast<int64_t>(half) - 1);
+    const double xc = g.fs[0] * (g.o[0] + 0.5 * static_cast<double>(nx) * g.h[0]);
+    const double xd = g.fs[0] * ((static_cast<double>(ic) + 0.5 - 0.5 * static_cast<double>(nx)) * g.h[0]);
+    double yy[TI], zz[TI];
 #pragma unroll
-    for (int a = 0; a < RA; ++a)
-#pragma unroll
-        for (int b = 0; b < RB; ++b) acc[a][b] = 0.f;
-
-    for (int j0 = 0; j0 < n; j0 += J) {
-        // (rows are ldp long, a multiple of 64: a chunk of 128 past it stages zeros it never sums)
-#pragma unroll
-        for (int it = 0; it < RA * J / 64; ++it) {
-            const int e = it * 256 + t;
-            const int row = e / kG, g = e % kG;
-            const int xg = min(x0 + row, nx - 1);
-            float4 c = make_float4(0.f, 0.f, 0.f, 0.f), sn = c;
-            if (J <= 64 || j0 + 4 * g < ldp) {
-                const float4 f = *reinterpret_cast<const float4*>(tx + static_cast<int64_t>(xg) * ldp + j0 + 4 * g);
-                c = make_float4(cos_rev(f.x), cos_rev(f.y), cos_rev(f.z), cos_rev(f.w));
-                sn = make_float4(sin_rev(f.x), sin_rev(f.y), sin_rev(f.z), sin_rev(f.w));
-            }
-            sx[row * kRow + g] = c;
-            sx[row * kRow + kG + g] = sn;
-        }
-#pragma unroll
-        for (int it = 0; it < RB * J / 64; ++it) {
-            const int e = it * 256 + t;
-            const int row = e / kG, g = e % kG;
-            const int64_t q = min(q0 + row, nq - 1);
-            const int64_t yy = q % ny, zz = q / ny;
-            float4 c = make_float4(0.f, 0.f, 0.f, 0.f), sn = c;
-            if (J <= 64 || j0 + 4 * g < ldp) {
-                const float4 fa = *reinterpret_cast<const float4*>(ty + yy * ldp + j0 + 4 * g);
-                const float4 fb = *reinterpret_cast<const float4*>(tz + zz * ldp + j0 + 4 * g);
-                const float4 f = make_float4(fa.x + fb.x, fa.y + fb.y, fa.z + fb.z, fa.w + fb.w);
-                c = make_float4(cos_rev(f.x), cos_rev(f.y), cos_rev(f.z), cos_rev(f.w));
-                sn = make_float4(sin_rev(f.x), sin_rev(f.y), sin_rev(f.z), sin_rev(f.w));
-                if (wt) {
-                    // modes past n carry no weight (their terms are not summed)
-                    const int j = j0 + 4 * g;
-                    const float4 wv = make_float4(j < n ? static_cast<float>(wt[j]) : 0.f,
-                                                  j + 1 < n ? static_cast<float>(wt[j + 1]) : 0.f,
-                                                  j + 2 < n ? static_cast<float>(wt[j + 2]) : 0.f,
-                                                  j + 3 < n ? static_cast<float>(wt[j + 3]) : 0.f);
-                    c = make_float4(wv.x * c.x, wv.y * c.y, wv.z * c.z, wv.w * c.w);
-                    sn = make_float4(wv.x * sn.x, wv.y * sn.y, wv.z * sn.z, wv.w * sn.w);
-                }
-            }
-            sq[row * kRow + g] = c;
-            sq[row * kRow + kG + g] = sn;
-        }
-        __syncthreads();
-        const int jn = min(J, n - j0);
-        const int j4 = jn >> 2;
-        for (int m = 0; m < j4; ++m) {
-            float4 xc[RA], xs[RA], qc[RB], qs[RB];
-#pragma unroll
-            for (int r = 0; r < RA; ++r) {
-                xc[r] = sx[(lx + 16 * r) * kRow + m];
-                xs[r] = sx[(lx + 16 * r) * kRow + kG + m];
-            }
-#pragma unroll
-            for (int r = 0; r < RB; ++r) {
-                qc[r] = sq[(lq + 4 * r) * kRow + m];
-                qs[r] = sq[(lq + 4 * r) * kRow + kG + m];
-            }
-#pragma unroll
-            for (int a = 0; a < RA; ++a)
-#pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    float v = acc[a][b];
-                    v = fmaf(xc[a].x, qc[b].x, v);
-                    v = fmaf(-xs[a].x, qs[b].x, v);
-                    v = fmaf(xc[a].y, qc[b].y, v);
-                    v = fmaf(-xs[a].y, qs[b].y, v);
-                    v = fmaf(xc[a].z, qc[b].z, v);
-                    v = fmaf(-xs[a].z, qs[b].z, v);
-                    v = fmaf(xc[a].w, qc[b].w, v);
-                    v = fmaf(-xs[a].w, qs[b].w, v);
-                    acc[a][b] = v;
-                }
-        }
-        const float* sxf = reinterpret_cast<const float*>(sx);
-        const float* sqf = reinterpret_cast<const float*>(sq);
-        for (int m = j4 * 4; m < jn; ++m) {
-#pragma unroll
-            for (int a = 0; a < RA; ++a)
-#pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    const float* rx = sxf + (lx + 16 * a) * kRow * 4;
-                    const float* rq = sqf + (lq + 4 * b) * kRow * 4;
-                    acc[a][b] = fmaf(rx[m], rq[m], acc[a][b]);
-                    acc[a][b] = fmaf(-rx[J + m], rq[J + m], acc[a][b]);
-                }
-        }
-        __syncthreads();
+    for (int i = 0; i < TI; ++i) {
+        const int64_t q = min(q0 + i * TS + r, g.nq - 1);
+        yy[i] = g.fs[1] * (g.o[1] + (static_cast<double>(q % g.ny) + 0.5) * g.h[1]);
+        zz[i] = g.fs[2] * (g.o[2] + (static_cast<double>(q / g.ny) + 0.5) * g.h[2]);
     }
 
+    typename T::Acc ae[TI], ao[TI];
 #pragma unroll
-    for (int a = 0; a < RA; ++a) {
-        const int x = x0 + lx + 16 * a;
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int b = 0; b < RB; ++b) {
-            const int64_t q = q0 + lq + 4 * b;
-            if (x < nx && q < nq) {
-                store_out(q * nx + x, amp * acc[a][b], epi, y, k, ind);
+        for (int e = 0; e < NE; ++e) {
+            ae[i][e] = 0.f;
+            ao[i][e] = 0.f;
+        }
+
+    // this wave's chunk of the modes (a multiple of 8 modes per chunk, whatever the tile)
+    const int64_t mc = 8 * ((n + 63) >> 6);
+    const int64_t j0 = min(w * mc, n), j1 = min(j0 + mc, n);
+    double4* const sm = reinterpret_cast<double4*>(smem) + w * kDgStage;
+    float* const sw = reinterpret_cast<float*>(smem + kDgWaves * kDgStage * 32) + w * kDgStage;
+    const double* const zy = g.z + n;
+    const double* const z3 = g.dim == 3 ? g.z + 2 * n : nullptr;
+
+    // modes past the chunk's end stage the table's last entry of the chunk; their row operands
+    // are set to zero below
+    auto fetch = [&](int64_t j) {
+        const int64_t jj = min(j + l, j1 - 1);
+        return make_double4(g.z[jj], zy[jj], z3 ? z3[jj] : 0.0, g.phi[jj] * kInvTwoPi);
+    };
+    auto fetch_w = [&](int64_t j) { return WT ? static_cast<float>(g.w[min(j + l, j1 - 1)]) : 1.f; };
+    double4 nm = make_double4(0.0, 0.0, 0.0, 0.0);
+    float nw = 1.f;
+    if (j0 < j1) {
+        nm = fetch(j0);
+        nw = fetch_w(j0);
+    }
+    for (int64_t jb = j0; jb < j1; jb += kDgStage) {
+        // the wave's own LDS, read and written in program order: compiler barriers suffice
+        __builtin_amdgcn_wave_barrier();
+        sm[l] = nm;
+        if (WT) sw[l] = nw;
+        __builtin_amdgcn_wave_barrier();
+        if (jb + kDgStage < j1) {
+            nm = fetch(jb + kDgStage);
+            nw = fetch_w(jb + kDgStage);
+        }
+        const int cnt = static_cast<int>(min<int64_t>(kDgStage, j1 - jb));
+        auto step = [&](int m, bool tail) {
+            const double4 p = sm[m + kk];
+            const float wj = WT ? sw[m + kk] : 1.f;
+            const float fb = static_cast<float>(__builtin_amdgcn_fract(p.x * xd));
+            const float cb = cos_rev(fb), sb = sin_rev(fb);
+            const double base = fma(p.x, xc, p.w);
+#pragma unroll
+            for (int i = 0; i < TI; ++i) {
+                const double ph = fma(p.z, zz[i], fma(p.y, yy[i], base));
+                const float f = static_cast<float>(__builtin_amdgcn_fract(ph));
+                float ca = cos_rev(f), sa = sin_rev(f);
+                if (WT) {
+                    ca *= wj;
+                    sa *= wj;
+                }
+                if (tail && m + kk >= cnt) ca = sa = 0.f;
+                ae[i] = T::mma(ca, cb, ae[i]);
+                ao[i] = T::mma(sa, sb, ao[i]);
+            }
+        };
+        int m = 0;
+#pragma unroll 4
+        for (; m + KS <= cnt; m += KS) step(m, false);
+        if (m < cnt) step(m, true);
+    }
+
+    // chunk sums -> LDS (element-major: lane-contiguous both ways), added in chunk order
+    float* const ss = reinterpret_cast<float*>(smem);
+    constexpr int kPart = 2 * TS * TS;  // floats per wave: E then O
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            ss[w * kPart + e * 64 + l] = ae[i][e];
+            ss[w * kPart + TS * TS + e * 64 + l] = ao[i][e];
+        }
+        __syncthreads();
+        for (int p = t; p < TS * TS; p += kDgWaves * 64) {
+            float se = ss[p], so = ss[TS * TS + p];
+#pragma unroll
+            for (int c = 1; c < kDgWaves; ++c) {
+                se += ss[c * kPart + p];
+                so += ss[c * kPart + TS * TS + p];
+            }
+            const int64_t col = i0 + (p & 63) % TS;
+            const int64_t q = q0 + i * TS + T::row(p >> 6, p & 63);
+            if (col < half && q < g.nq) {
+                const int64_t mirror = nx - 1 - col;
+                epi_store(q * nx + col, g.amp * (se - so), epi, g.y, g.k, g.ind);
+                if (mirror != col) epi_store(q * nx + mirror, g.amp * (se + so), epi, g.y, g.k, g.ind);
             }
         }
     }
 }
 
-template <int RA, int RB, int J>
-__global__ __launch_bounds__(256, 2) void k_direct_grid(const float* __restrict__ tx, const float* __restrict__ ty,
-                                                       const float* __restrict__ tz, const double* __restrict__ wt,
-                                                       int n, int64_t ldp, int nx, int ny, int64_t nq, int nxt,
-                                                       float amp, Epi epi, float* __restrict__ y,
-                                                       float* __restrict__ k, uint8_t* __restrict__ ind)
+template <int TS, int TI, bool WT>
+__global__ __launch_bounds__(kDgWaves * 64) void k_direct_grid(DirectGrid g, Epi epi, int64_t tiles_i, int64_t tiles)
 {
-    using S = DirectShape<RA, RB, J>;
-    __shared__ float4 sx[S::X4];
-    __shared__ float4 sq[S::Q4];
-    const int64_t bid = blockIdx.x;
-    direct_tile<RA, RB, J>(tx, ty, tz, wt, n, ldp, nx, ny, nq, static_cast<int>(bid % nxt) * 16 * RA,
-                           (bid / nxt) * 16 * RB, amp, epi, y, k, ind, sx, sq);
+    __shared__ __attribute__((aligned(16))) char smem[DgShape<TS>::BYTES];
+    const int64_t bid = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    if (bid >= tiles) return;  // the whole block
+    direct_tile<TS, TI, WT>(g, epi, bid % tiles_i * TS, bid / tiles_i * (TI * TS), smem);
 }
 
 // Persistent batched form: blocks pull (instance, tile) work items from one atomic counter
 // until the queue is drained.
-__global__ __launch_bounds__(256, 2) void k_direct_batch(const DirectBatchItem* __restrict__ items, int n_inst,
-                                                        int64_t total, unsigned long long* counter)
+__global__ __launch_bounds__(kDgWaves * 64) void k_direct_batch(const DirectBatchItem* __restrict__ items, int n_inst,
+                                                               int64_t total, unsigned long long* counter)
 {
-    using S = DirectShape<4, 4, 32>;
-    __shared__ float4 sx[S::X4];
-    __shared__ float4 sq[S::Q4];
+    __shared__ __attribute__((aligned(16))) char smem[DgShape<32>::BYTES];
     __shared__ unsigned long long s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1ull);
@@ -214,8 +242,10 @@ __global__ __launch_bounds__(256, 2) void k_direct_batch(const DirectBatchItem* 
         }
         const DirectBatchItem& b = items[lo];
         const int64_t local = it - b.item0;
-        direct_tile<4, 4, 32>(b.tx, b.ty, b.tz, b.w, b.n, b.ldp, b.nx, b.ny, b.nq, static_cast<int>(local % b.nxt) * kDgB,
-                              (local / b.nxt) * kDgB, b.amp, b.epi, b.y, b.k, b.ind, sx, sq);
+        const int64_t i0 = local % b.tiles_i * 32, q0 = local / b.tiles_i * 64;
+        if (b.g.w) direct_tile<32, 2, true>(b.g, b.epi, i0, q0, smem);
+        else direct_tile<32, 2, false>(b.g, b.epi, i0, q0, smem);
+        __syncthreads();  // the sums in LDS are read before the next item stages over them
     }
 }
 
@@ -507,33 +537,35 @@ __global__ __launch_bounds__(256) void k_epilogue_scalar(const float* __restrict
 
 }  // namespace
 
-hipError_t launch_direct_grid_f32(const float* tx, const float* ty, const float* tz, const double* w, int64_t n,
-                                  int64_t ldp, const int64_t* gn, float amp, const Epi& epi, float* y, float* k,
-                                  uint8_t* ind, hipStream_t s)
+namespace {
+template <int TS, int TI>
+hipError_t launch_direct_tile(const DirectGrid& g, const Epi& epi, hipStream_t s)
 {
-    const int nx = static_cast<int>(gn[0]), ny = static_cast<int>(gn[1]);
-    const int64_t nq = gn[1] * gn[2];
-    // the widest tile that still gives two blocks per CU (512), else 1 x 1 cells per lane
-    auto blocks_of = [&](int sx_, int sq_) -> int64_t {
-        return static_cast<int64_t>((nx + sx_ - 1) / sx_) * ((nq + sq_ - 1) / sq_);
-    };
-    int v = 3;
-    if (blocks_of(64, 128) >= 512) v = 0;
-    else if (blocks_of(64, 64) >= 512) v = 1;
-    else if (blocks_of(32, 32) >= 512) v = 2;
-    static constexpr int kSx[4] = {64, 64, 32, 16}, kSq[4] = {128, 64, 32, 16};
-    const int nxt = (nx + kSx[v] - 1) / kSx[v];
-    const int64_t blocks = blocks_of(kSx[v], kSq[v]);
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 g(static_cast<unsigned>(blocks));
-    const int nn = static_cast<int>(n);
-    switch (v) {
-    case 0: hipLaunchKernelGGL((k_direct_grid<4, 8, 32>), g, dim3(256), 0, s, tx, ty, tz, w, nn, ldp, nx, ny, nq, nxt, amp, epi, y, k, ind); break;
-    case 1: hipLaunchKernelGGL((k_direct_grid<4, 4, 32>), g, dim3(256), 0, s, tx, ty, tz, w, nn, ldp, nx, ny, nq, nxt, amp, epi, y, k, ind); break;
-    case 2: hipLaunchKernelGGL((k_direct_grid<2, 2, 64>), g, dim3(256), 0, s, tx, ty, tz, w, nn, ldp, nx, ny, nq, nxt, amp, epi, y, k, ind); break;
-    default: hipLaunchKernelGGL((k_direct_grid<1, 1, 256>), g, dim3(256), 0, s, tx, ty, tz, w, nn, ldp, nx, ny, nq, nxt, amp, epi, y, k, ind); break;
-    }
+    const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2;
+    const int64_t ti = (half + TS - 1) / TS, tq = (g.nq + TI * TS - 1) / (TI * TS);
+    const int64_t tiles = ti * tq;
+    const int64_t gy = (tiles + 0x3fffffff) / 0x40000000;  // grids of more than 2^30 tiles fold into y
+    if (gy > 65535) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>((tiles + gy - 1) / gy), static_cast<unsigned>(gy));
+    if (g.w)
+        hipLaunchKernelGGL((k_direct_grid<TS, TI, true>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
+    else
+        hipLaunchKernelGGL((k_direct_grid<TS, TI, false>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream_t s)
+{
+    const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2;
+    auto tiles = [&](int64_t rows, int64_t cols) { return ((half + cols - 1) / cols) * ((g.nq + rows - 1) / rows); };
+    // A tile's time does not depend on how many there are until the CUs are full, and grows with
+    // its area: the widest tile that fills most of the 256 CUs.  4,096 modes, us per call for
+    // 64 x 32 / 32 x 32 / 16 x 16: 64^3 (128 tiles of 32 x 32) 91 / 53 / 42; 1024 x 512 (256) 96 / 58
+    // / 78; 128^3 (1,024) 187 / 193 / 262; 3,000 modes on 100 x 90 x 80 (450) 76 / 80 / 109.
+    if (tiles(64, 32) >= 160) return launch_direct_tile<32, 2>(g, epi, s);
+    if (tiles(32, 32) >= 192) return launch_direct_tile<32, 1>(g, epi, s);
+    return launch_direct_tile<16, 1>(g, epi, s);
 }
 
 ModeSlices direct_grid_f64_slices(const int64_t* gn, int64_t n)
@@ -638,14 +670,14 @@ int points_mode_slices(int64_t P, int64_t n)
 hipError_t launch_direct_batch(const DirectBatchItem* items, int n_inst, int64_t total, unsigned long long* counter,
                                int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_direct_batch, dim3(grid), dim3(256), 0, s, items, n_inst, total, counter);
+    hipLaunchKernelGGL(k_direct_batch, dim3(grid), dim3(kDgWaves * 64), 0, s, items, n_inst, total, counter);
     return hipGetLastError();
 }
 
 int direct_batch_blocks_per_cu()
 {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_direct_batch, 256, 0) != hipSuccess) return 1;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_direct_batch, kDgWaves * 64, 0) != hipSuccess) return 1;
     return nb > 0 ? nb : 1;
 }
 

@@ -203,10 +203,23 @@ hipError_t launch_mode_params(const double* z, const double* phi, int dim, int64
                               const double* ell, double* out, hipStream_t s);
 
 // ---------------------------------------------------------------- direct kernels
-// `w`: device per-mode weights [n] or nullptr (all 1).
-hipError_t launch_direct_grid_f32(const float* tx, const float* ty, const float* tz, const double* w, int64_t n,
-                                  int64_t ldp, const int64_t* gn, float amp, const Epi& epi,
-                                  float* y, float* k, uint8_t* ind, hipStream_t s);
+// One FP32 grid sum: the (axis-aligned) mode table, the grid and the outputs (each may be nullptr).
+struct DirectGrid {
+    const double* z;    // [dim][n]
+    const double* phi;  // [n]
+    const double* w;    // [n] or nullptr (all 1)
+    double fs[3];       // 1 / (2 pi ell) per axis, 0 for an absent axis
+    double o[3], h[3];  // grid origin and spacing
+    int64_t n;          // modes
+    int64_t ny, nq;     // y cells; ny nz
+    int32_t nx, dim;
+    float amp;
+    float* y;
+    float* k;
+    uint8_t* ind;
+};
+DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind);
+hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream_t s);
 // Mode slices of the FP64 grid sum: grids too small to fill the device split the modes
 // into `slices` runs of `mslice` (slices = 1: no split).
 struct ModeSlices {
@@ -374,25 +387,15 @@ inline bool sep_batch_generates(int method, bool d3)
 }
 
 struct DirectBatchItem {
-    const float* tx;
-    const float* ty;
-    const float* tz;
-    const double* w;  // per-mode weights or nullptr
-    float* y;         // outputs of the instance, each may be nullptr
-    float* k;
-    uint8_t* ind;
+    DirectGrid g;
     Epi epi;
-    int64_t ldp;
-    int64_t nq;       // ny * nz
-    int64_t item0;
-    int32_t n, nx, ny, nxt;  // nxt: 64-cell tiles along x
-    float amp;
-    int32_t pad_;
+    int64_t item0;    // first work item; tiles of 64 rows x 32 columns, columns fastest
+    int64_t tiles_i;  // tiles along x
 };
 hipError_t launch_direct_batch(const DirectBatchItem* items, int n_inst, int64_t total,
                                unsigned long long* counter, int grid, hipStream_t s);
 int direct_batch_blocks_per_cu();
-constexpr int kDirectTile = 64;  // cells per tile side of the direct grid kernel
+constexpr int kDirectTile = 64;  // cells per tile side of the direct batch kernel
 
 // Batched per-axis tables: one launch over many AxisTableArgs (device array).  blk[b]
 // (device, total_blocks entries) = (descriptor << 40) | work block within that table, for
