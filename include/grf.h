@@ -58,8 +58,8 @@ extern "C" {
 #define GRF_DIRECT_F64 1    /* FP64 throughout (small problems, reference-grade) */
 #define GRF_SEP_BF16 2      /* matrix-core contraction, bf16 tables, one pass */
 #define GRF_SEP_F16 3       /* matrix-core contraction, fp16 tables, one pass */
-#define GRF_SEP_BF16_X3 4   /* bf16 hi+lo split tables, three passes */
-#define GRF_SEP_F16_X3 5    /* fp16 hi+lo split tables, three passes */
+#define GRF_SEP_BF16_X3 4   /* bf16 hi+lo split operands, three passes */
+#define GRF_SEP_F16_X3 5    /* fp16 hi+lo split operands, three passes */
 /* point sums only (eval_field_points, eval_pluri_points): the two forms GRF_DIRECT_F32 picks from */
 #define GRF_DIRECT_F32_BINNED 6    /* points binned in cells, FP64 phase per (mode, cell), FP32 offsets */
 #define GRF_DIRECT_F32_POINTWISE 7 /* FP64 phase per (mode, point) */
@@ -196,8 +196,8 @@ int eval_field_grid_ws_size(const grf_modes* modes, const grf_grid* grid, int me
  *                     tables (DIRECT_F32 forms its operands on chip and leaves them
  *                     unwritten); for DIRECT_F64 on grids too small to fill the device (under
  *                     131,072 cells) the FP64 partial sums of its mode slices; for the
- *                     separable methods on grids of fewer default tiles than the device
- *                     has CUs, the FP32 sums of the mode slices that the contraction is split
+ *                     separable methods on grids of too few blocks to fill the device's
+ *                     CUs, the FP32 sums of the mode slices that the contraction is split
  *                     into (at most 32 MiB; the slices are added in order by a second pass
  *                     that applies the epilogue).  A workspace smaller than that but large
  *                     enough for the tables runs the contraction unsplit (the same field up

@@ -13,7 +13,7 @@ CSRC = PKG / "csrc"
 OBJ = PKG / "_build"
 LIB = PKG / "libgrf.so"
 PROBE_LIB = PKG / "libgrf_probe.so"
-SOURCES = ["api.cpp", "modes.cpp", "tables.hip", "direct.hip", "sep.hip", "adjoint.hip", "batch.hip", "krige.hip", "noalloc.hip", "points.hip"]
+SOURCES = ["api.cpp", "modes.cpp", "tables.hip", "direct.hip", "sep.hip", "fold.hip", "adjoint.hip", "batch.hip", "krige.hip", "noalloc.hip", "points.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

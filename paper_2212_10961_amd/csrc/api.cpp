@@ -209,6 +209,14 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
             w.split_bytes = c.used - before;
         }
     }
+    // the hi+lo forms' default evaluation (fold.hip) keeps its tables, never larger than the ones
+    // above, and its slice sums here instead
+    if (is_hilo(method)) {
+        const FoldWs f = fold_ws(g->n[0], g->n[1], g->n[2], ldp, dim, true);
+        const size_t tables = c.used;
+        c.used = std::max(c.used, f.partial + f.split_bytes);
+        w.split_bytes = c.used - tables;
+    }
     w.bytes = c.used;
     return w;
 }
@@ -400,6 +408,11 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
         GRF_HIP(launch_direct_grid_f32(direct_grid_args(modes, grid, y, k, ind), e, s));
         return GRF_OK;
     }
+    if (is_hilo(method) && tile < 0) {
+        GRF_HIP(launch_fold(direct_grid_args(modes, grid, y, k, ind), padded_modes(modes->n), is_bf16(method), e, ws,
+                            allow_split, true, s));
+        return GRF_OK;
+    }
     GRF_HIP(build_tables(modes, grid, method, w, s));
     if (is_sep(method)) {
         SepArgs a = sep_args(modes, grid, method, tile, e, y, k, ind, w);
@@ -502,9 +515,9 @@ static size_t pluri_grid_ws(const grf_modes* m1, const grf_modes* m2, const grf_
                             bool own_y2)
 {
     const int64_t C = g->n[0] * g->n[1] * g->n[2];
-    // separable forms: both fields' tables at once (one table launch, one contraction launch)
+    // one-pass separable forms: both fields' tables at once (one table launch, one contraction)
     const size_t b1 = grid_ws(m1, g, method, nullptr).bytes, b2 = grid_ws(m2, g, method, nullptr).bytes;
-    const size_t t = is_sep(method) ? b1 + b2 : std::max(b1, b2);
+    const size_t t = is_sep(method) && !is_hilo(method) ? b1 + b2 : std::max(b1, b2);
     const size_t f = align256(sizeof(float) * size_t(C));
     return align256(kRuleBytes) + rot_ws_bytes(m1) + rot_ws_bytes(m2) + (own_y1 ? f : 0) + (own_y2 ? f : 0) + t;
 }
@@ -554,7 +567,7 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
     GRF_HIP(aligned_modes(m1, k1, s, &a1));
     GRF_HIP(aligned_modes(m2, k2, s, &a2));
     GRF_HIP(launch_rule_tables(*rule, rt, s));
-    if (is_sep(method)) {
+    if (is_sep(method) && !is_hilo(method)) {
         // both fields: one launch of the six (2-D: four) tables, one of the contraction
         const GridWs w1 = grid_ws(&a1, grid, method, tabs);
         const GridWs w2 = grid_ws(&a2, grid, method, static_cast<char*>(tabs) + w1.bytes);

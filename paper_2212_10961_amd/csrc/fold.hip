@@ -1,0 +1,590 @@
+// Split-precision grid sum folded over the grid's middle (the hi+lo separable forms).
+//
+// Cell centres are symmetric about the middle along x: with x = xc + d the mirrored cell has
+// offset -d, and with B = a_x d and F = a_x xc + a_y y + a_z z + psi (Sec. 4.1 phases),
+//   Y(+-d) = E -+ O,   E = sum_j w_j cos F cos B,   O = sum_j w_j sin F sin B,
+// so each pair of cells costs two real multiply-adds per mode, half of the complex product
+// P_z Q of the separable form.  E and O are matrix products on the 16-bit matrix cores (rows
+// the (y, z) pairs, columns the nx / 2 offsets, K the modes), every factor split hi + lo and
+// the three products hi hi, hi lo, lo hi accumulated in FP32.
+//
+// Operands: per-axis tables (phases formed and reduced in FP64), eight modes of one axis point in
+// 64 contiguous bytes, [ldp / 8][points][64 B].  The columns (and the rows of a 2-D grid) are
+// stored split, [cos hi | cos lo | sin hi | sin lo] of eight 16-bit values each, and go straight
+// from global memory into LDS.  In 3-D the row operand is the product of the y and z
+// factors, tables of FP32 cosines and sines multiplied and split on chip.
+//
+// A block is eight waves, two per SIMD, with different roles: waves 0-3 only read fragments and
+// issue matrix products, waves 4-7 only fill LDS stages of 16 modes, up to three stages ahead
+// (four stage buffers, one barrier per stage).  The vector work of the row product (about 90
+// instructions per 64 rows and octet) then runs beside the other waves' matrix products instead
+// of between them, and the matrix waves, whose next fragments are always ready, read half a
+// stage ahead.
+//
+// What bounds it: 256^3 x 4,096 modes take 0.44 ms; the same kernel without the row products' vector
+// work takes 0.35 ms, where the matrix cores are busy 73% of the cycles at the 1.6 GHz that the
+// chip holds under this load (1.2 PFLOP/s, the rate of a large library product).  One barrier for
+// all eight waves after loading, splitting and multiplying in turn (no roles) ran at 0.60 ms.
+// One call, the separable form with the complex product -> this one: 256^3 0.88 -> 0.47 ms;
+// 203 x 171 x 85 x 3,000 modes 0.41 -> 0.11 ms; 128^3 0.19 -> 0.11 ms; 1500 x 1200 x 2,048 modes 0.12 ->
+// 0.069 ms; relative error against FP64 5.0e-7 on 128^3 both ways, 8.7e-7 -> 4.4e-7 on the ragged
+// grid.  (The hardware cosine in the tables would save 5 us and add 10% to the error.)
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "grf_internal.h"
+
+namespace grf {
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+
+constexpr int kFs = 16;           // modes per stage
+constexpr int kRowB = 4 * kFs * 2;  // LDS bytes of one operand row: cos hi, cos lo, sin hi, sin lo
+
+template <bool BF>
+__device__ __forceinline__ f32x16 mma(uint4 a, uint4 b, f32x16 c)
+{
+    if constexpr (BF)
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                       0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0,
+                                                      0);
+}
+
+// Two values as hi words (rounded to nearest) and lo words (the remainders, rounded).
+template <bool BF>
+__device__ __forceinline__ void split2(float v0, float v1, uint32_t& hi, uint32_t& lo)
+{
+    const f2 v = {v0, v1};
+    if constexpr (BF) {
+        const b2 h = __builtin_convertvector(v, b2);
+        hi = __builtin_bit_cast(uint32_t, h);
+        const f2 r = {v0 - __builtin_bit_cast(float, hi << 16), v1 - __builtin_bit_cast(float, hi & 0xffff0000u)};
+        lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, b2));
+    } else {
+        const h2 h = __builtin_convertvector(v, h2);
+        hi = __builtin_bit_cast(uint32_t, h);
+        // v - hi, the fp16 operand converted by the instruction (one instead of two)
+        float r0, r1;
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi), "v"(v0));
+        asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi), "v"(v1));
+        const f2 r = {r0, r1};
+        lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, h2));
+    }
+}
+
+template <bool BF>
+__device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& lo)
+{
+    split2<BF>(v[0], v[1], hi.x, lo.x);
+    split2<BF>(v[2], v[3], hi.y, lo.y);
+    split2<BF>(v[4], v[5], hi.z, lo.z);
+    split2<BF>(v[6], v[7], hi.w, lo.w);
+}
+
+__device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
+
+struct FoldTabs {
+    const double* z;
+    const double* phi;
+    const double* w;
+    double fs[3], o[3], h[3];
+    int64_t n, ldp, half, ny, nz;  // nz = 0: no z table
+    double nx;
+    uint4* tb;
+    uint4* ty;
+    uint4* tz;
+    int64_t bb, by;  // thread blocks of the column and y tables
+};
+
+// One thread: eight modes of one point of one axis (64 contiguous bytes); blockIdx.y = octet.
+// Columns, and the rows of a 2-D grid, are stored split; y and z of a 3-D grid as FP32.
+template <bool BF>
+__global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
+{
+    constexpr double kInvTwoPi = 0.15915494309189533576888376337251;
+    int64_t b = blockIdx.x;
+    const int axis = b < a.bb ? 0 : (b < a.bb + a.by ? 1 : 2);
+    b -= axis == 0 ? 0 : (axis == 1 ? a.bb : a.bb + a.by);
+    const int64_t rows = axis == 0 ? a.half : (axis == 1 ? a.ny : a.nz);
+    const int64_t i = b * 256 + threadIdx.x;
+    if (i >= rows) return;
+    const int64_t oct = blockIdx.y;
+    const double* const z = a.z + axis * a.n;
+    const double xc = a.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
+    const double x = axis == 0 ? a.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
+                     : axis == 1 ? a.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
+                                 : a.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
+    float c[8], s[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const int64_t j = oct * 8 + m;
+        c[m] = s[m] = 0.f;  // modes past n add nothing
+        if (j < a.n) {
+            double t = z[j] * x;
+            if (axis == 1) t += fma(a.z[j], xc, a.phi[j] * kInvTwoPi);
+            double sd, cd;
+            sincospi(2.0 * __builtin_amdgcn_fract(t), &sd, &cd);
+            const double w = axis == 1 && a.w ? a.w[j] : 1.0;
+            c[m] = static_cast<float>(w * cd);
+            s[m] = static_cast<float>(w * sd);
+        }
+    }
+    const bool split = axis == 0 || (axis == 1 && a.nz == 0);
+    uint4 o[4];
+    if (split) {
+        split8<BF>(c, o[0], o[1]);
+        split8<BF>(s, o[2], o[3]);
+    } else {
+        o[0] = __builtin_bit_cast(uint4, make_float4(c[0], c[1], c[2], c[3]));
+        o[1] = __builtin_bit_cast(uint4, make_float4(c[4], c[5], c[6], c[7]));
+        o[2] = __builtin_bit_cast(uint4, make_float4(s[0], s[1], s[2], s[3]));
+        o[3] = __builtin_bit_cast(uint4, make_float4(s[4], s[5], s[6], s[7]));
+    }
+    uint4* const out = (axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz)) + oct * rows * 4 + (split ? i * 4 : (axis == 1 ? i : i * 4));
+    const int64_t step = !split && axis == 1 ? rows : 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) out[q * step] = o[q];
+}
+
+struct FoldArgs {
+    const uint4* tb;
+    const uint4* ty;
+    const uint4* tz;
+    int64_t nx, half, ny, nz, nq;
+    int64_t stages, per;  // 16-mode stages in all and per slice, multiples of 4
+    int64_t tiles_i, tiles, items;  // column tiles; tiles of one slice; tiles of all slices
+    float amp;
+    float* y;
+    float* k;
+    uint8_t* ind;
+    float* partial;  // raw sums [slice][nq nx] of a launch whose modes are split, or nullptr
+};
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef float raw_f4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(4))) raw_f4 scalar_f4;  // constant memory: read by scalar loads
+
+// 16 bytes per lane from a uniform base plus an unsigned 32-bit byte offset below `bytes`, to LDS
+// bytes 16 l .. of `s`.  The buffer form: a pending global_load_lds counts as a flat access, and
+// the compiler then makes every later wait of the wave a wait for all its loads.
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t bytes, uint32_t off, char* s)
+{
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, static_cast<int>(bytes), 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)s, 16, static_cast<int>(off), 0, 0, 0);
+}
+
+// Waits until at most VM vector-memory and LG LDS / scalar operations of the wave are under way (15:
+// no wait on those).  The builtin, unlike inline assembly, is seen by the compiler's own
+// accounting, which then adds no second wait.
+template <int VM, int LG>
+__device__ __forceinline__ void wait_counts()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (LG << 8) | ((VM >> 4) << 14));
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
+// A barrier that waits for nothing by itself: each role states what it has to wait for.
+__device__ __forceinline__ void bare_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
+// Block: rows q0 .. q0 + BM - 1, columns i0 .. i0 + BN - 1; four matrix waves (2 x 2), each TM x TN
+// tiles of 32 x 32 (two accumulators each), and four operand waves.
+template <int TM, int TN, bool BF, bool D3>
+__global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
+{
+    constexpr int BM = 64 * TM, BN = 64 * TN;
+    constexpr int kA = BM * kRowB, kB = BN * kRowB;  // bytes of one stage
+    static_assert(BM == 128, "each operand wave makes 32 rows");
+    __shared__ __attribute__((aligned(16))) char sa[4 * kA];
+    __shared__ __attribute__((aligned(16))) char sb[4 * kB];
+    const int l = threadIdx.x & 63, h = l >> 5, lr = l & 31;
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    // Consecutive blocks run on different XCDs, each with its own L2: every XCD takes a run of
+    // consecutive work items (slice by slice, columns fastest), whose blocks read the same table
+    // stages at the same time.
+    const int64_t item = static_cast<int64_t>(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (item >= a.items) return;  // the whole block
+    const int64_t slice = item / a.tiles, tile = item - slice * a.tiles;
+    const int64_t i0 = tile % a.tiles_i * BN, q0 = tile / a.tiles_i * BM;
+    const int64_t s0 = slice * a.per, s1 = min(a.stages, s0 + a.per);
+    const int ns = static_cast<int>(s1 - s0);  // a multiple of 4, at least 4
+
+    if (w >= 4) {
+        // ---- operand waves.  Stage t: columns by direct loads, issued three stages ahead; rows by
+        // direct loads too in 2-D, in 3-D from the y and z factors: fetched into registers four
+        // stages ahead, multiplied, split and stored two stages ahead.  Past the last stage the
+        // last one is loaded again, into buffers that nothing reads any more.
+        const int pw = w - 4;
+        constexpr int KB = BN / 32, KA = D3 ? 1 : BM / 32;  // direct-load instructions (8 rows each) per wave
+        uint32_t offb[KB], offa[KA];
+        int ldb[KB], lda[KA];
+        auto source = [&](int rb, int64_t first, int64_t rows) {
+            const int r = rb * 8 + (l >> 3);
+            const int c = (l & 7) ^ swz(r);  // logical chunk: octet, kind (four lanes read 64 bytes)
+            const int64_t i = min(first + r, rows - 1);
+            return static_cast<uint32_t>(((c >> 2) * rows + i) * 64 + (c & 3) * 16);
+        };
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            const int rb = pw * KB + k;
+            offb[k] = source(rb, i0, a.half);
+            ldb[k] = rb * 8 * kRowB;
+        }
+        const char* gb = reinterpret_cast<const char*>(a.tb) + 2 * s0 * a.half * 64;
+        const char* ga = reinterpret_cast<const char*>(a.ty) + 2 * s0 * a.ny * 64;
+        const char* gz = D3 ? reinterpret_cast<const char*>(a.tz) + 2 * s0 * a.nz * 64 : nullptr;
+        const int64_t stepb = 128 * a.half, stepa = 128 * a.ny, stepz = 128 * a.nz;
+        // 3-D: this wave makes octet pw % 2 of the rows 64 (pw / 2) + l
+        const int row = (pw >> 1) * 64 + l, oct = pw & 1;
+        uint32_t offy = 0, offz = 0;
+        bool onez = false;  // the wave's rows lie in one z-slice: its z factors are uniform
+        if constexpr (D3) {
+            const int64_t q = min(q0 + row, a.nq - 1);
+            offy = static_cast<uint32_t>(oct * a.ny * 64 + q % a.ny * 16);
+            offz = static_cast<uint32_t>((oct * a.nz + q / a.ny) * 64);
+            const int64_t za = min(q0 + (pw >> 1) * 64, a.nq - 1) / a.ny, zb = min(q0 + (pw >> 1) * 64 + 63, a.nq - 1) / a.ny;
+            onez = za == zb;
+            gz += (oct * a.nz + za) * 64;  // (per-lane offsets are taken from the first row's)
+            offz -= static_cast<uint32_t>((oct * a.nz + za) * 64);
+        } else {
+#pragma unroll
+            for (int k = 0; k < KA; ++k) {
+                const int rb = pw * KA + k;
+                offa[k] = source(rb, q0, a.ny);
+                lda[k] = rb * 8 * kRowB;
+            }
+        }
+        int left_d = ns - 1, left_f = ns - 1, left_z = ns - 1;  // stages the pointers may still advance
+        auto direct = [&](int t) {
+            char* const bb = sb + (t & 3) * kB;
+#pragma unroll
+            for (int k = 0; k < KB; ++k) load_to_lds(gb, static_cast<uint32_t>(stepb), offb[k], bb + ldb[k]);
+            gb += left_d > 0 ? stepb : 0;
+            if constexpr (!D3) {
+                char* const ba = sa + (t & 3) * kA;
+#pragma unroll
+                for (int k = 0; k < KA; ++k) load_to_lds(ga, static_cast<uint32_t>(stepa), offa[k], ba + lda[k]);
+                ga += left_d > 0 ? stepa : 0;
+            }
+            --left_d;
+        };
+        struct Four {
+            float4 v[4];
+        };
+        // y factors of one stage: four planes of 16 bytes per row (contiguous over the lanes)
+        auto fetch_y = [&](Four& r) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r.v[c] = *reinterpret_cast<const float4*>(ga + c * (a.ny * 16) + offy);
+            ga += left_f > 0 ? stepa : 0;
+            --left_f;
+        };
+        // z factors; a uniform and constant address is read by scalar loads
+        auto fetch_z = [&](Four& r, auto onez_c) {
+            if constexpr (decltype(onez_c)::value) {
+                const scalar_f4* z = (const scalar_f4*)gz;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r.v[c] = __builtin_bit_cast(float4, z[c]);
+            } else {
+                const float4* z = reinterpret_cast<const float4*>(gz + offz);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r.v[c] = z[c];
+            }
+            gz += left_z > 0 ? stepz : 0;
+            --left_z;
+        };
+        const int x = swz(row);
+        char* const wbase = sa + row * kRowB;
+        auto put = [&](int t, const Four& y4, const Four& z4) {
+            const float* v = reinterpret_cast<const float*>(y4.v);
+            const float* z = reinterpret_cast<const float*>(z4.v);
+            float c[8], s[8];
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                c[m] = fmaf(v[m], z[m], -(v[8 + m] * z[8 + m]));
+                s[m] = fmaf(v[8 + m], z[m], v[m] * z[8 + m]);
+            }
+            uint4 o[4];
+            split8<BF>(c, o[0], o[1]);
+            split8<BF>(s, o[2], o[3]);
+            char* const base = wbase + (t & 3) * kA;
+#pragma unroll
+            for (int kind = 0; kind < 4; ++kind) *reinterpret_cast<uint4*>(base + (((4 * oct + kind) ^ x) << 4)) = o[kind];
+        };
+        direct(0);
+        direct(1);
+        direct(2);
+        auto stages = [&](auto onez_c) {
+            constexpr bool kOne = decltype(onez_c)::value;
+            Four y0, y1, z0, z1;
+            if constexpr (D3) {
+                fetch_y(y0);
+                fetch_y(y1);
+                fetch_z(z0, onez_c);
+                fetch_z(z1, onez_c);
+                put(0, y0, z0);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_z(z0, onez_c);
+                __builtin_amdgcn_sched_barrier(0);
+                put(1, y1, z1);
+            }
+            wait_counts<0, 0>();
+            if constexpr (D3) {
+                fetch_y(y0);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_y(y1);
+            }
+            bare_barrier();
+            // y holds stage t + 2's factors and takes stage t + 4's; zc holds stage t + 2's, zn
+            // takes stage t + 3's
+            auto stage = [&](int t, Four& y, const Four& zc, Four& zn) {
+                if constexpr (D3) {
+                    fetch_z(zn, onez_c);
+                    __builtin_amdgcn_sched_barrier(0);
+                    put(t + 2, y, zc);
+                    __builtin_amdgcn_sched_barrier(0);
+                    direct(t + 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch_y(y);
+                    // stage t + 2's direct loads have landed: at most the fetches of the
+                    // previous iteration and this one's loads are still under way
+                    constexpr int kZ = kOne ? 0 : 4;
+                    wait_counts<KB + 8 + kZ, 0>();
+                } else {
+                    direct(t + 3);
+                    wait_counts<KB + KA, 15>();
+                }
+                bare_barrier();
+            };
+            for (int t = 0; t < ns; t += 2) {
+                stage(t, y0, z0, z1);
+                stage(t + 1, y1, z1, z0);
+            }
+        };
+        if (D3 && !onez) stages(std::false_type{});
+        else stages(std::true_type{});
+        wait_counts<0, 15>();  // no load may land in LDS after the block's end
+        return;
+    }
+
+    // ---- matrix waves
+    const int wm = w >> 1, wn = w & 1;
+    f32x16 ae[TM][TN], ao[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                ae[i][j][e] = 0.f;
+                ao[i][j][e] = 0.f;
+            }
+    // Fragments of half a stage: the cosines (kinds 0, 1: hi, lo) or the sines (2, 3).
+    struct Frag {
+        uint4 a[TM][2], b[TN][2];
+    };
+    int fa[TM][4], fb[TN][4];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int kind = 0; kind < 4; ++kind) {
+            const int r = (wm * TM + i) * 32 + lr;
+            fa[i][kind] = r * kRowB + (((4 * h + kind) ^ swz(r)) << 4);
+        }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int kind = 0; kind < 4; ++kind) {
+            const int r = (wn * TN + j) * 32 + lr;
+            fb[j][kind] = r * kRowB + (((4 * h + kind) ^ swz(r)) << 4);
+        }
+    auto read = [&](int buf, int half, Frag& f) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                f.a[i][x] = *reinterpret_cast<const uint4*>(sa + buf * kA + fa[i][2 * half + x]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                f.b[j][x] = *reinterpret_cast<const uint4*>(sb + buf * kB + fb[j][2 * half + x]);
+        }
+    };
+    auto mac = [&](const Frag& f, f32x16(&acc)[TM][TN]) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p)  // hi hi, hi lo, lo hi
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = mma<BF>(f.a[i][p == 2], f.b[j][p == 1], acc[i][j]);
+    };
+    // the reads of the next half ride along the products of this one
+    auto interleave = [&]() {
+        constexpr int NR = 2 * (TM + TN), NM = 3 * TM * TN;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, NM - NR > 0 ? NM - NR : 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Frag f0, f1;
+    bare_barrier();
+    read(0, 0, f0);
+    for (int t = 0; t < ns; t += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            read(u, 1, f1);
+            mac(f0, ae);
+            interleave();
+            // stage t + u + 1 is complete since the last barrier (past the end: unused values)
+            read((u + 1) & 3, 0, f0);
+            mac(f1, ao);
+            interleave();
+            bare_barrier();
+        }
+    }
+
+    const bool raw = a.partial != nullptr;
+    float* const y = raw ? a.partial + slice * (a.nq * a.nx) : a.y;
+    float* const kk = raw ? nullptr : a.k;
+    uint8_t* const ind = raw ? nullptr : a.ind;
+    const float amp = raw ? 1.f : a.amp;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int64_t col = i0 + (wn * TN + j) * 32 + lr, mirror = a.nx - 1 - col;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int64_t q = q0 + (wm * TM + i) * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+                if (col >= a.half || q >= a.nq) continue;
+                const float ev = ae[i][j][e], ov = ao[i][j][e];
+                epi_store(q * a.nx + col, amp * (ev - ov), epi, y, kk, ind);
+                if (mirror != col) epi_store(q * a.nx + mirror, amp * (ev + ov), epi, y, kk, ind);
+            }
+        }
+}
+
+template <int TM, int TN>
+hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, hipStream_t s)
+{
+    FoldArgs a = a0;
+    a.tiles_i = (a.half + 64 * TN - 1) / (64 * TN);
+    a.tiles = a.tiles_i * ((a.nq + 64 * TM - 1) / (64 * TM));
+    a.items = a.tiles * slices;
+    const int64_t blocks = (a.items + 7) / 8 * 8;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 g(static_cast<unsigned>(blocks)), b(512);
+    if (a.tz) {
+        if (bf) hipLaunchKernelGGL((k_fold<TM, TN, true, true>), g, b, 0, s, a, epi);
+        else hipLaunchKernelGGL((k_fold<TM, TN, false, true>), g, b, 0, s, a, epi);
+    } else {
+        if (bf) hipLaunchKernelGGL((k_fold<TM, TN, true, false>), g, b, 0, s, a, epi);
+        else hipLaunchKernelGGL((k_fold<TM, TN, false, false>), g, b, 0, s, a, epi);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split)
+{
+    FoldWs w;
+    const int64_t half = (nx + 1) / 2, nq = ny * nz, C = nq * nx;
+    w.ty = align256(size_t(half) * ldp * 8);
+    w.tz = w.ty + align256(size_t(ny) * ldp * 8);
+    w.partial = w.tz + align256(size_t(dim == 3 ? nz : 0) * ldp * 8);
+    // 128 rows x 128 columns per block, 64 columns where that covers fewer
+    w.wide = (half + 127) / 128 * 128 == (half + 63) / 64 * 64;
+    const int64_t cols = w.wide ? 128 : 64;
+    const int64_t blocks = ((half + cols - 1) / cols) * ((nq + 127) / 128);
+    // One block per CU at a time (LDS): launches of at most half the 256 CUs split the modes
+    // into slices of at least eight stages (128 modes) that fill them; the slices' sums take at
+    // most 32 MiB.
+    constexpr int64_t kCUs = 256, kMaxBytes = int64_t(32) << 20;
+    const int64_t quads = ldp / (4 * kFs);  // slices are whole groups of four stages
+    int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads / 2), kMaxBytes / (4 * C)) : 1;
+    if (sl < 2) sl = 1;
+    w.per = 4 * ((quads + sl - 1) / sl);
+    w.slices = static_cast<int>((4 * quads + w.per - 1) / w.per);
+    w.split_bytes = w.slices > 1 ? align256(sizeof(float) * size_t(w.slices) * size_t(C)) : 0;
+    return w;
+}
+
+hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
+                       hipStream_t s)
+{
+    const FoldWs w = fold_ws(d.nx, d.ny, d.nq / d.ny, ldp, d.dim, split);
+    char* const base = static_cast<char*>(ws);
+    FoldTabs t{};
+    t.z = d.z;
+    t.phi = d.phi;
+    t.w = d.w;
+    for (int a = 0; a < 3; ++a) {
+        t.fs[a] = d.fs[a];
+        t.o[a] = d.o[a];
+        t.h[a] = d.h[a];
+    }
+    t.n = d.n;
+    t.ldp = ldp;
+    t.half = (static_cast<int64_t>(d.nx) + 1) / 2;
+    t.ny = d.ny;
+    t.nz = d.dim == 3 ? d.nq / d.ny : 0;
+    t.nx = static_cast<double>(d.nx);
+    t.tb = reinterpret_cast<uint4*>(base);
+    t.ty = reinterpret_cast<uint4*>(base + w.ty);
+    t.tz = t.nz ? reinterpret_cast<uint4*>(base + w.tz) : nullptr;
+    t.bb = (t.half + 255) / 256;
+    t.by = (t.ny + 255) / 256;
+    const int64_t tb = t.bb + t.by + (t.nz + 255) / 256, oct = ldp / 8;
+    if (tb > 0x7fffffff || oct > 65535) return hipErrorInvalidValue;
+    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(oct));
+    if (bf) hipLaunchKernelGGL(k_fold_tables<true>, tg, dim3(256), 0, s, t);
+    else hipLaunchKernelGGL(k_fold_tables<false>, tg, dim3(256), 0, s, t);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+
+    FoldArgs a{};
+    a.tb = t.tb;
+    a.ty = t.ty;
+    a.tz = t.tz;
+    a.nx = d.nx;
+    a.half = t.half;
+    a.ny = d.ny;
+    a.nz = t.nz;
+    a.nq = d.nq;
+    a.stages = ldp / kFs;
+    a.per = w.per;
+    a.amp = d.amp;
+    a.y = d.y;
+    a.k = d.k;
+    a.ind = d.ind;
+    a.partial = w.slices > 1 ? reinterpret_cast<float*>(base + w.partial) : nullptr;
+    TimedScope scope(s, timed);
+    e = w.wide ? launch_tile<2, 2>(a, epi, bf, w.slices, s) : launch_tile<2, 1>(a, epi, bf, w.slices, s);
+    if (e != hipSuccess || w.slices == 1) return e;
+    return launch_points_reduce(a.partial, w.slices, d.nq * d.nx, d.amp, epi, d.y, d.k, d.ind, s);
+}
+
+}  // namespace grf

@@ -220,6 +220,20 @@ struct DirectGrid {
 };
 DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind);
 hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream_t s);
+
+// ---------------------------------------------------------------- folded split-precision grid sum (fold.hip)
+// Offsets of its tables (columns at 0) and slice sums in the workspace, and its launch plan;
+// `split` = false plans without the slices.
+struct FoldWs {
+    size_t ty, tz, partial;
+    size_t split_bytes;  // of the slice sums
+    bool wide;           // blocks of 128 columns, else 64
+    int slices;          // mode slices (1: no split) of `per` stages each
+    int64_t per;
+};
+FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split);
+hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
+                       hipStream_t s);
 // Mode slices of the FP64 grid sum: grids too small to fill the device split the modes
 // into `slices` runs of `mslice` (slices = 1: no split).
 struct ModeSlices {
