@@ -193,12 +193,10 @@ int eval_field_grid_ws_size(const grf_modes* modes, const grf_grid* grid, int me
  *                     At least one output must be non-NULL.  epi may be NULL when
  *                     k and ind are NULL.
  *   ws, ws_bytes      device workspace of eval_field_grid_ws_size bytes: the per-axis
- *                     tables (DIRECT_F32 forms its operands on chip and leaves them
- *                     unwritten); for DIRECT_F64 on grids too small to fill the device (under
- *                     131,072 cells) the FP64 partial sums of its mode slices; for the
- *                     separable methods on grids of too few blocks to fill the device's
- *                     CUs, the FP32 sums of the mode slices that the contraction is split
- *                     into (at most 32 MiB; the slices are added in order by a second pass
+ *                     tables (the direct methods form their operands on chip; DIRECT_F64
+ *                     keeps the sums of its mode slices there); for the separable methods
+ *                     on grids of too few blocks to fill the device's CUs, the FP32 sums of
+ *                     the mode slices that the contraction is split into (at most 32 MiB; the slices are added in order by a second pass
  *                     that applies the epilogue).  A workspace smaller than that but large
  *                     enough for the tables runs the contraction unsplit (the same field up
  *                     to FP32 summation order); below that GRF_ENOMEM.  Contents on entry

@@ -186,8 +186,6 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
         for (int a = 0; a < 3; ++a) w.t[a] = c.take<float>(size_t(g->n[a]) * ldp);
     } else if (method == GRF_DIRECT_F64) {
         for (int a = 0; a < 3; ++a) w.t[a] = c.take<double>(size_t(g->n[a]) * ldp);
-        const ModeSlices ms = direct_grid_f64_slices(g->n, m->n);
-        if (ms.slices > 1) w.partial = c.take<double>(size_t(ms.slices) * size_t(g->n[0] * g->n[1] * g->n[2]));
     } else if (is_sep(method)) {
         const bool hilo = is_hilo(method);
         if (dim == 2) {
@@ -260,8 +258,6 @@ int grid_table_descs(const grf_modes* m, const grf_grid* g, int method, const Gr
         if (a >= m->dim) t.z = nullptr;  // axis absent: zero phase
         if (method == GRF_DIRECT_F32) {
             t.format = TF_REV_F32;
-        } else if (method == GRF_DIRECT_F64) {
-            t.format = TF_REV_F64;
         } else {
             const bool hilo = is_hilo(method), bf = is_bf16(method);
             // single-pass operands are rounded to fp16/bf16 (2^-11 or 2^-8): the hardware
@@ -304,7 +300,8 @@ DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, flo
     d.n = m->n;
     d.nx = static_cast<int32_t>(g->n[0]);
     d.dim = m->dim;
-    d.amp = static_cast<float>(m->sigma * std::sqrt(2.0 / static_cast<double>(m->n)));
+    d.amp64 = m->sigma * std::sqrt(2.0 / static_cast<double>(m->n));
+    d.amp = static_cast<float>(d.amp64);
     d.y = y;
     d.k = k;
     d.ind = ind;
@@ -403,9 +400,12 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
 {
     GridWs w = grid_ws(modes, grid, method, ws);
     if (!allow_split && w.split_bytes) w.partial = nullptr;  // the workspace holds the tables only
-    if (method == GRF_DIRECT_F32) {  // operands are formed on chip: no tables
+    if (!is_sep(method)) {  // operands are formed on chip: no tables
         TimedScope timed(s);
-        GRF_HIP(launch_direct_grid_f32(direct_grid_args(modes, grid, y, k, ind), e, s));
+        const DirectGrid d = direct_grid_args(modes, grid, y, k, ind);
+        GRF_HIP(method == GRF_DIRECT_F32
+                    ? launch_direct_grid_f32(d, e, s)
+                    : launch_direct_grid_f64(d, e, static_cast<double*>(ws), w.bytes / sizeof(double), s));
         return GRF_OK;
     }
     if (is_hilo(method) && tile < 0) {
@@ -414,18 +414,9 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
         return GRF_OK;
     }
     GRF_HIP(build_tables(modes, grid, method, w, s));
-    if (is_sep(method)) {
-        SepArgs a = sep_args(modes, grid, method, tile, e, y, k, ind, w);
-        a.timed = true;
-        GRF_HIP(launch_sep(a, s));
-        return GRF_OK;
-    }
-    TimedScope timed(s);
-    const double amp64 = modes->sigma * std::sqrt(2.0 / static_cast<double>(modes->n));
-    GRF_HIP(launch_direct_grid_f64(static_cast<const double*>(w.t[0]), static_cast<const double*>(w.t[1]),
-                                   static_cast<const double*>(w.t[2]), modes->w, modes->n, padded_modes(modes->n),
-                                   grid->n, amp64, e, 0.0, y, k, ind, nullptr, nullptr,
-                                   static_cast<double*>(w.partial), s));
+    SepArgs a = sep_args(modes, grid, method, tile, e, y, k, ind, w);
+    a.timed = true;
+    GRF_HIP(launch_sep(a, s));
     return GRF_OK;
 }
 
@@ -755,13 +746,12 @@ int eval_field_grid_f64(const grf_modes* modes, const grf_grid* grid, double mu,
     hipStream_t s = static_cast<hipStream_t>(stream);
     grf_modes am;
     GRF_HIP(aligned_modes(modes, ws, s, &am));
-    const GridWs w = grid_ws(&am, grid, GRF_DIRECT_F64, static_cast<char*>(ws) + rb);
-    GRF_HIP(build_tables(&am, grid, GRF_DIRECT_F64, w, s));
-    const double amp64 = modes->sigma * std::sqrt(2.0 / static_cast<double>(modes->n));
-    GRF_HIP(launch_direct_grid_f64(static_cast<const double*>(w.t[0]), static_cast<const double*>(w.t[1]),
-                                   static_cast<const double*>(w.t[2]), modes->w, modes->n, padded_modes(modes->n),
-                                   grid->n, amp64, Epi{}, mu, nullptr, nullptr, nullptr, y64, k64,
-                                   static_cast<double*>(w.partial), s));
+    DirectGrid d = direct_grid_args(&am, grid, nullptr, nullptr, nullptr);
+    d.mu64 = mu;
+    d.y64 = y64;
+    d.k64 = k64;
+    GRF_HIP(launch_direct_grid_f64(d, Epi{}, reinterpret_cast<double*>(static_cast<char*>(ws) + rb),
+                                   (need - rb) / sizeof(double), s));
     return GRF_OK;
 }
 

@@ -50,6 +50,12 @@ __device__ __forceinline__ void store_out(int64_t c, float yv, const Epi& e, flo
 // tabulated phases) took, before -> after, one call: 128^3 x 4,096 modes 566 -> 174 us, a weighted
 // 517 x 301 x 2,048 table 120 -> 23 us, 64 x 64 x 1,000 27 -> 13 us; relative error against FP64
 // on 128^3 1.6e-6 -> 4.5e-7 (the phases are summed in FP64 and the chunks are shorter).
+//
+// DIRECT_F64 is the same tile on FP64 operands (sincospi of the FP64 fraction) and the FP64 matrix
+// cores; its operands, not the products, take the time, so larger grids share each column
+// operand among four row tiles.  Tabulated phases and one cospi per mode and cell took, before ->
+// after, one call: 64 x 64 x 1,000 modes 22 -> 18 us (what the binding's host work takes),
+// 128 x 128 x 2,048 72 -> 20, 300 x 200 x 4,096 420 -> 69, 64^3 x 4,096 1,537 -> 146 us.
 constexpr int kDgWaves = 8;    // waves of a block = mode chunks of every sum
 constexpr int kDgStage = 64;   // modes staged in LDS per wave
 static_assert(kDirectTile == 64, "the batch tile is 64 rows x 32 columns (64 cells)");
@@ -58,11 +64,12 @@ __device__ __forceinline__ float sin_rev(float r) { return __builtin_amdgcn_sinf
 
 typedef float dg_f16 __attribute__((ext_vector_type(16)));
 typedef float dg_f4 __attribute__((ext_vector_type(4)));
+typedef double dg_d4 __attribute__((ext_vector_type(4)));
 
-template <int TS>
+template <class R, int TS>
 struct DgTile;
 template <>
-struct DgTile<32> {
+struct DgTile<float, 32> {
     using Acc = dg_f16;
     static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
     {
@@ -71,7 +78,7 @@ struct DgTile<32> {
     static __device__ __forceinline__ int row(int e, int l) { return 8 * (e >> 2) + 4 * (l >> 5) + (e & 3); }
 };
 template <>
-struct DgTile<16> {
+struct DgTile<float, 16> {
     using Acc = dg_f4;
     static __device__ __forceinline__ Acc mma(float a, float b, Acc c)
     {
@@ -79,21 +86,60 @@ struct DgTile<16> {
     }
     static __device__ __forceinline__ int row(int e, int l) { return 4 * (l >> 4) + e; }
 };
+template <>
+struct DgTile<double, 16> {
+    using Acc = dg_d4;
+    static __device__ __forceinline__ Acc mma(double a, double b, Acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    // (the FP64 form interleaves its output rows across the four lane groups)
+    static __device__ __forceinline__ int row(int e, int l) { return 4 * e + (l >> 4); }
+};
+
+// Cosine and sine of a phase in revolutions: the hardware's on the fraction in FP32, or FP64.
+__device__ __forceinline__ void cos_sin_rev(double t, float& c, float& s)
+{
+    const float f = static_cast<float>(__builtin_amdgcn_fract(t));
+    c = cos_rev(f);
+    s = sin_rev(f);
+}
+__device__ __forceinline__ void cos_sin_rev(double t, double& c, double& s)
+{
+    sincospi(2.0 * __builtin_amdgcn_fract(t), &s, &c);
+}
+
+// Outputs of cell c.
+__device__ __forceinline__ void dg_store(const DirectGrid& g, const Epi& epi, int64_t c, float sum)
+{
+    epi_store(c, g.amp * sum, epi, g.y, g.k, g.ind);
+}
+__device__ __forceinline__ void dg_store(const DirectGrid& g, const Epi& epi, int64_t c, double sum)
+{
+    if (g.partial64) {  // one slice of the modes: its raw sums
+        g.partial64[static_cast<int64_t>(blockIdx.z) * (g.nq * g.nx) + c] = sum;
+        return;
+    }
+    const double yv = g.amp64 * sum;
+    if (g.y64) g.y64[c] = yv;
+    if (g.k64) g.k64[c] = exp(g.mu64 + yv);
+    if (g.y || g.k || g.ind) epi_store(c, static_cast<float>(yv), epi, g.y, g.k, g.ind);
+}
 
 // LDS of one block: the waves' mode stages, later the chunk sums of one row tile.
-template <int TS>
+template <class R, int TS>
 struct DgShape {
-    static constexpr int kModeB = kDgWaves * kDgStage * (4 * 8 + 4);
-    static constexpr int kSumB = kDgWaves * 2 * TS * TS * 4;
+    static constexpr int kModeB = kDgWaves * kDgStage * (4 * 8 + static_cast<int>(sizeof(R)));
+    static constexpr int kSumB = kDgWaves * 2 * TS * TS * static_cast<int>(sizeof(R));
     static constexpr int BYTES = kModeB > kSumB ? kModeB : kSumB;
 };
 
 // Rows q0 .. q0 + TI TS - 1, columns i0 .. i0 + TS - 1 (offsets from the middle; column i is cell
-// i and its mirror nx - 1 - i).  `smem`: DgShape<TS>::BYTES bytes, 16-byte aligned.  Whole block.
-template <int TS, int TI, bool WT>
+// i and its mirror nx - 1 - i).  `smem`: DgShape<R, TS>::BYTES bytes, 16-byte aligned.  Whole block.
+template <class R, int TS, int TI, bool WT>
 __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi, int64_t i0, int64_t q0, char* smem)
 {
-    using T = DgTile<TS>;
+    using T = DgTile<R, TS>;
     constexpr int KS = 64 / TS;         // modes per matrix step
     constexpr int NE = TS * TS / 64;    // accumulator elements per lane
     constexpr double kInvTwoPi = 0.15915494309189533576888376337251;
@@ -120,15 +166,18 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            ae[i][e] = 0.f;
-            ao[i][e] = 0.f;
+            ae[i][e] = R(0);
+            ao[i][e] = R(0);
         }
 
     // this wave's chunk of the modes (a multiple of 8 modes per chunk, whatever the tile)
-    const int64_t mc = 8 * ((n + 63) >> 6);
-    const int64_t j0 = min(w * mc, n), j1 = min(j0 + mc, n);
+    // (FP64: of its slice's modes)
+    const int64_t n0 = sizeof(R) == 8 ? static_cast<int64_t>(blockIdx.z) * g.mslice : 0;
+    const int64_t n1 = sizeof(R) == 8 ? min(n, n0 + g.mslice) : n;
+    const int64_t mc = 8 * ((n1 - n0 + 63) >> 6);
+    const int64_t j0 = min(n0 + w * mc, n1), j1 = min(j0 + mc, n1);
     double4* const sm = reinterpret_cast<double4*>(smem) + w * kDgStage;
-    float* const sw = reinterpret_cast<float*>(smem + kDgWaves * kDgStage * 32) + w * kDgStage;
+    R* const sw = reinterpret_cast<R*>(smem + kDgWaves * kDgStage * 32) + w * kDgStage;
     const double* const zy = g.z + n;
     const double* const z3 = g.dim == 3 ? g.z + 2 * n : nullptr;
 
@@ -138,9 +187,9 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
         const int64_t jj = min(j + l, j1 - 1);
         return make_double4(g.z[jj], zy[jj], z3 ? z3[jj] : 0.0, g.phi[jj] * kInvTwoPi);
     };
-    auto fetch_w = [&](int64_t j) { return WT ? static_cast<float>(g.w[min(j + l, j1 - 1)]) : 1.f; };
+    auto fetch_w = [&](int64_t j) { return WT ? static_cast<R>(g.w[min(j + l, j1 - 1)]) : R(1); };
     double4 nm = make_double4(0.0, 0.0, 0.0, 0.0);
-    float nw = 1.f;
+    R nw = R(1);
     if (j0 < j1) {
         nm = fetch(j0);
         nw = fetch_w(j0);
@@ -158,20 +207,19 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
         const int cnt = static_cast<int>(min<int64_t>(kDgStage, j1 - jb));
         auto step = [&](int m, bool tail) {
             const double4 p = sm[m + kk];
-            const float wj = WT ? sw[m + kk] : 1.f;
-            const float fb = static_cast<float>(__builtin_amdgcn_fract(p.x * xd));
-            const float cb = cos_rev(fb), sb = sin_rev(fb);
+            const R wj = WT ? sw[m + kk] : R(1);
+            R cb, sb;
+            cos_sin_rev(p.x * xd, cb, sb);
             const double base = fma(p.x, xc, p.w);
 #pragma unroll
             for (int i = 0; i < TI; ++i) {
-                const double ph = fma(p.z, zz[i], fma(p.y, yy[i], base));
-                const float f = static_cast<float>(__builtin_amdgcn_fract(ph));
-                float ca = cos_rev(f), sa = sin_rev(f);
+                R ca, sa;
+                cos_sin_rev(fma(p.z, zz[i], fma(p.y, yy[i], base)), ca, sa);
                 if (WT) {
                     ca *= wj;
                     sa *= wj;
                 }
-                if (tail && m + kk >= cnt) ca = sa = 0.f;
+                if (tail && m + kk >= cnt) ca = sa = R(0);
                 ae[i] = T::mma(ca, cb, ae[i]);
                 ao[i] = T::mma(sa, sb, ao[i]);
             }
@@ -183,8 +231,8 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
     }
 
     // chunk sums -> LDS (element-major: lane-contiguous both ways), added in chunk order
-    float* const ss = reinterpret_cast<float*>(smem);
-    constexpr int kPart = 2 * TS * TS;  // floats per wave: E then O
+    R* const ss = reinterpret_cast<R*>(smem);
+    constexpr int kPart = 2 * TS * TS;  // values per wave: E then O
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
         __syncthreads();
@@ -195,7 +243,7 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
         }
         __syncthreads();
         for (int p = t; p < TS * TS; p += kDgWaves * 64) {
-            float se = ss[p], so = ss[TS * TS + p];
+            R se = ss[p], so = ss[TS * TS + p];
 #pragma unroll
             for (int c = 1; c < kDgWaves; ++c) {
                 se += ss[c * kPart + p];
@@ -205,20 +253,36 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
             const int64_t q = q0 + i * TS + T::row(p >> 6, p & 63);
             if (col < half && q < g.nq) {
                 const int64_t mirror = nx - 1 - col;
-                epi_store(q * nx + col, g.amp * (se - so), epi, g.y, g.k, g.ind);
-                if (mirror != col) epi_store(q * nx + mirror, g.amp * (se + so), epi, g.y, g.k, g.ind);
+                dg_store(g, epi, q * nx + col, se - so);
+                if (mirror != col) dg_store(g, epi, q * nx + mirror, se + so);
             }
         }
     }
 }
 
-template <int TS, int TI, bool WT>
+template <class R, int TS, int TI, bool WT>
 __global__ __launch_bounds__(kDgWaves * 64) void k_direct_grid(DirectGrid g, Epi epi, int64_t tiles_i, int64_t tiles)
 {
-    __shared__ __attribute__((aligned(16))) char smem[DgShape<TS>::BYTES];
+    __shared__ __attribute__((aligned(16))) char smem[DgShape<R, TS>::BYTES];
     const int64_t bid = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
     if (bid >= tiles) return;  // the whole block
-    direct_tile<TS, TI, WT>(g, epi, bid % tiles_i * TS, bid / tiles_i * (TI * TS), smem);
+    direct_tile<R, TS, TI, WT>(g, epi, bid % tiles_i * TS, bid / tiles_i * (TI * TS), smem);
+}
+
+// FP64 sums of the mode slices, added in slice order.
+__global__ __launch_bounds__(256) void k_grid_reduce_f64(const double* __restrict__ partial, int slices, int64_t C,
+                                                        DirectGrid g, Epi epi)
+{
+    const int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (c >= C) return;
+    double v[8];  // at most eight slices: every load in flight
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = partial[static_cast<int64_t>(q < slices ? q : 0) * C + c];
+    double sum = v[0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q)
+        if (q < slices) sum += v[q];
+    dg_store(g, epi, c, sum);
 }
 
 // Persistent batched form: blocks pull (instance, tile) work items from one atomic counter
@@ -226,7 +290,7 @@ __global__ __launch_bounds__(kDgWaves * 64) void k_direct_grid(DirectGrid g, Epi
 __global__ __launch_bounds__(kDgWaves * 64) void k_direct_batch(const DirectBatchItem* __restrict__ items, int n_inst,
                                                                int64_t total, unsigned long long* counter)
 {
-    __shared__ __attribute__((aligned(16))) char smem[DgShape<32>::BYTES];
+    __shared__ __attribute__((aligned(16))) char smem[DgShape<float, 32>::BYTES];
     __shared__ unsigned long long s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(counter, 1ull);
@@ -243,101 +307,10 @@ __global__ __launch_bounds__(kDgWaves * 64) void k_direct_batch(const DirectBatc
         const DirectBatchItem& b = items[lo];
         const int64_t local = it - b.item0;
         const int64_t i0 = local % b.tiles_i * 32, q0 = local / b.tiles_i * 64;
-        if (b.g.w) direct_tile<32, 2, true>(b.g, b.epi, i0, q0, smem);
-        else direct_tile<32, 2, false>(b.g, b.epi, i0, q0, smem);
+        if (b.g.w) direct_tile<float, 32, 2, true>(b.g, b.epi, i0, q0, smem);
+        else direct_tile<float, 32, 2, false>(b.g, b.epi, i0, q0, smem);
         __syncthreads();  // the sums in LDS are read before the next item stages over them
     }
-}
-
-// ---------------------------------------------------------------------------- grid, FP64
-// One thread per cell, FP64 per-axis fractions summed and reduced in FP64, cos by
-// the device library's cospi.  For small problems and as a reference-grade path.  Grids
-// too small to fill the device split the modes over blockIdx.y slices of `mslice` modes:
-// each slice writes its raw FP64 sums to partial[slice][C] and k_grid_reduce_f64 adds them
-// in slice order.
-__device__ __forceinline__ void grid_out_f64(int64_t c, double yv, const Epi& epi, double mu64,
-                                             float* __restrict__ y, float* __restrict__ k,
-                                             uint8_t* __restrict__ ind, double* __restrict__ y64,
-                                             double* __restrict__ k64)
-{
-    if (y64) y64[c] = yv;
-    if (k64) k64[c] = exp(mu64 + yv);
-    if (y || k || ind) store_out(c, static_cast<float>(yv), epi, y, k, ind);
-}
-
-__global__ __launch_bounds__(256) void k_direct_grid_f64(const double* __restrict__ tx, const double* __restrict__ ty,
-                                                        const double* __restrict__ tz, const double* __restrict__ wt,
-                                                        int n, int64_t ldp, int nx,
-                                                        int ny, int64_t C, double amp, Epi epi, double mu64,
-                                                        float* __restrict__ y, float* __restrict__ k,
-                                                        uint8_t* __restrict__ ind, double* __restrict__ y64,
-                                                        double* __restrict__ k64, int mslice,
-                                                        double* __restrict__ partial)
-{
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    const int64_t i = c % nx, q = c / nx;
-    const int64_t jy = q % ny, kz = q / ny;
-    const double* rx = tx + i * ldp;
-    const double* ry = ty + jy * ldp;
-    const double* rz = tz + kz * ldp;
-    const int j0 = static_cast<int>(blockIdx.y) * mslice;
-    const int j1 = min(n, j0 + mslice);
-    double s = 0.0;
-    auto term = [&](double fx, double fy, double fz, double wj) {
-        double f = fx + fy + fz;
-        f = __builtin_amdgcn_fract(f);  // x - floor(x) in one FP64 instruction
-        s += wj * cospi(2.0 * f);
-    };
-    // Eight modes' table entries are loaded ahead of their terms; the sum keeps mode order.
-    constexpr int kMG = 8;
-    int j = j0;
-    for (; j + kMG <= j1; j += kMG) {
-        double fx[kMG], fy[kMG], fz[kMG], ww[kMG];
-#pragma unroll
-        for (int u = 0; u < kMG; ++u) {
-            fx[u] = rx[j + u];
-            fy[u] = ry[j + u];
-            fz[u] = rz[j + u];
-        }
-        if (wt) {
-#pragma unroll
-            for (int u = 0; u < kMG; ++u) ww[u] = wt[j + u];
-        } else {
-#pragma unroll
-            for (int u = 0; u < kMG; ++u) ww[u] = 1.0;
-        }
-#pragma unroll
-        for (int u = 0; u < kMG; ++u) term(fx[u], fy[u], fz[u], ww[u]);
-    }
-    for (; j < j1; ++j) term(rx[j], ry[j], rz[j], wt ? wt[j] : 1.0);
-    if (partial) {
-        partial[static_cast<int64_t>(blockIdx.y) * C + c] = s;
-        return;
-    }
-    grid_out_f64(c, amp * s, epi, mu64, y, k, ind, y64, k64);
-}
-
-__global__ __launch_bounds__(256) void k_grid_reduce_f64(const double* __restrict__ partial, int slices, int64_t C,
-                                                        double amp, Epi epi, double mu64, float* __restrict__ y,
-                                                        float* __restrict__ k, uint8_t* __restrict__ ind,
-                                                        double* __restrict__ y64, double* __restrict__ k64)
-{
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    // Sixteen slice loads are in flight at a time; the adds keep slice order.
-    constexpr int kGroup = 16;
-    double s = 0.0;
-    int q = 0;
-    for (; q + kGroup <= slices; q += kGroup) {
-        double v[kGroup];
-#pragma unroll
-        for (int u = 0; u < kGroup; ++u) v[u] = partial[static_cast<int64_t>(q + u) * C + c];
-#pragma unroll
-        for (int u = 0; u < kGroup; ++u) s += v[u];
-    }
-    for (; q < slices; ++q) s += partial[static_cast<int64_t>(q) * C + c];
-    grid_out_f64(c, amp * s, epi, mu64, y, k, ind, y64, k64);
 }
 
 // ---------------------------------------------------------------------------- points
@@ -538,19 +511,19 @@ __global__ __launch_bounds__(256) void k_epilogue_scalar(const float* __restrict
 }  // namespace
 
 namespace {
-template <int TS, int TI>
-hipError_t launch_direct_tile(const DirectGrid& g, const Epi& epi, hipStream_t s)
+template <class R, int TS, int TI>
+hipError_t launch_direct_tile(const DirectGrid& g, const Epi& epi, hipStream_t s, int slices = 1)
 {
     const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2;
     const int64_t ti = (half + TS - 1) / TS, tq = (g.nq + TI * TS - 1) / (TI * TS);
     const int64_t tiles = ti * tq;
     const int64_t gy = (tiles + 0x3fffffff) / 0x40000000;  // grids of more than 2^30 tiles fold into y
     if (gy > 65535) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>((tiles + gy - 1) / gy), static_cast<unsigned>(gy));
+    const dim3 grid(static_cast<unsigned>((tiles + gy - 1) / gy), static_cast<unsigned>(gy), static_cast<unsigned>(slices));
     if (g.w)
-        hipLaunchKernelGGL((k_direct_grid<TS, TI, true>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
+        hipLaunchKernelGGL((k_direct_grid<R, TS, TI, true>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
     else
-        hipLaunchKernelGGL((k_direct_grid<TS, TI, false>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
+        hipLaunchKernelGGL((k_direct_grid<R, TS, TI, false>), grid, dim3(kDgWaves * 64), 0, s, g, epi, ti, tiles);
     return hipGetLastError();
 }
 }  // namespace
@@ -563,41 +536,33 @@ hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream
     // its area: the widest tile that fills most of the 256 CUs.  4,096 modes, us per call for
     // 64 x 32 / 32 x 32 / 16 x 16: 64^3 (128 tiles of 32 x 32) 91 / 53 / 42; 1024 x 512 (256) 96 / 58
     // / 78; 128^3 (1,024) 187 / 193 / 262; 3,000 modes on 100 x 90 x 80 (450) 76 / 80 / 109.
-    if (tiles(64, 32) >= 160) return launch_direct_tile<32, 2>(g, epi, s);
-    if (tiles(32, 32) >= 192) return launch_direct_tile<32, 1>(g, epi, s);
-    return launch_direct_tile<16, 1>(g, epi, s);
+    if (tiles(64, 32) >= 160) return launch_direct_tile<float, 32, 2>(g, epi, s);
+    if (tiles(32, 32) >= 192) return launch_direct_tile<float, 32, 1>(g, epi, s);
+    return launch_direct_tile<float, 16, 1>(g, epi, s);
 }
 
-ModeSlices direct_grid_f64_slices(const int64_t* gn, int64_t n)
+hipError_t launch_direct_grid_f64(const DirectGrid& g0, const Epi& epi, double* ws, size_t ws_doubles, hipStream_t s)
 {
-    // about 1024 blocks in all, at least 32 modes per slice, at most 64 slices
-    const int64_t blocks = (gn[0] * gn[1] * gn[2] + 255) / 256;
-    ModeSlices r{1, n};
-    if (blocks <= 0 || n <= 0 || blocks >= 512) return r;
-    int64_t sl = std::min<int64_t>(std::min<int64_t>((1024 + blocks - 1) / blocks, n / 32), 64);
-    if (sl <= 1) return r;
-    r.mslice = (n + sl - 1) / sl;
-    r.slices = static_cast<int>((n + r.mslice - 1) / r.mslice);
-    return r;
-}
-
-hipError_t launch_direct_grid_f64(const double* tx, const double* ty, const double* tz, const double* w, int64_t n,
-                                  int64_t ldp, const int64_t* gn, double amp, const Epi& epi, double mu64, float* y,
-                                  float* k, uint8_t* ind, double* y64, double* k64, double* partial, hipStream_t s)
-{
-    const int64_t C = gn[0] * gn[1] * gn[2];
-    const int64_t blocks = (C + 255) / 256;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const ModeSlices ms = direct_grid_f64_slices(gn, n);
-    if (ms.slices > 1 && !partial) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_direct_grid_f64, dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(ms.slices)),
-                       dim3(256), 0, s, tx, ty, tz, w, static_cast<int>(n), ldp, static_cast<int>(gn[0]),
-                       static_cast<int>(gn[1]), C, amp, epi, mu64, y, k, ind, y64, k64, static_cast<int>(ms.mslice),
-                       ms.slices > 1 ? partial : nullptr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || ms.slices == 1) return e;
-    hipLaunchKernelGGL(k_grid_reduce_f64, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, partial, ms.slices, C,
-                       amp, epi, mu64, y, k, ind, y64, k64);
+    DirectGrid g = g0;
+    g.mslice = g.n;
+    g.partial64 = nullptr;
+    const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2, C = g.nq * g.nx;
+    // an operand costs several matrix steps: four row tiles per column operand once they fill the CUs
+    if (((half + 15) / 16) * ((g.nq + 63) / 64) >= 256) return launch_direct_tile<double, 16, 4>(g, epi, s);
+    // few tiles: slices of at least 128 modes spread the operands over more CUs (a second launch
+    // adds the slices in order), where the workspace holds their sums
+    const int64_t tiles = ((half + 15) / 16) * ((g.nq + 15) / 16);
+    int64_t sl = std::min<int64_t>(std::min<int64_t>(128 / tiles, 8), g.n / 128);
+    sl = std::min<int64_t>(sl, static_cast<int64_t>(ws_doubles) / C);
+    if (sl < 2) return launch_direct_tile<double, 16, 1>(g, epi, s);
+    g.mslice = (g.n + sl - 1) / sl;
+    g.partial64 = ws;
+    const int slices = static_cast<int>((g.n + g.mslice - 1) / g.mslice);
+    const hipError_t e = launch_direct_tile<double, 16, 1>(g, epi, s, slices);
+    if (e != hipSuccess) return e;
+    g.partial64 = nullptr;
+    hipLaunchKernelGGL(k_grid_reduce_f64, dim3(static_cast<unsigned>((C + 255) / 256)), dim3(256), 0, s, ws, slices, C,
+                       g, epi);
     return hipGetLastError();
 }
 

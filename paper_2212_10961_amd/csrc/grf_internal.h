@@ -124,7 +124,6 @@ struct Carve {
 // ---------------------------------------------------------------- table formats
 enum TableFormat : int {
     TF_REV_F32 = 0,   // float: frac(a x + psi) in revolutions
-    TF_REV_F64 = 1,   // double: frac(a x + psi)
     TF_CPLX_F32 = 2,  // float2: (cos, sin)(2 pi frac)
     TF_F16 = 3,       // half2 (re, s*im), s = +1 or -1 (conj)
     TF_F16_HILO = 4,  // two half2 tables: hi and lo parts
@@ -168,8 +167,7 @@ int64_t axis_table_blocks(const AxisTableArgs& a);  // 256-thread work blocks on
 struct GridWs {
     void* t[3] = {nullptr, nullptr, nullptr};
     void* tlo[3] = {nullptr, nullptr, nullptr};
-    void* partial = nullptr;  // DIRECT_F64 on small grids, FP64; separable mode split, FP32:
-                              // per-slice sums
+    void* partial = nullptr;  // separable mode split: per-slice FP32 sums
     int slices = 1;           // separable mode split: slices of `pairs` stage pairs each
     int64_t pairs = 0;
     size_t split_bytes = 0;   // bytes of the separable split's sums (the last part of `bytes`)
@@ -203,7 +201,8 @@ hipError_t launch_mode_params(const double* z, const double* phi, int dim, int64
                               const double* ell, double* out, hipStream_t s);
 
 // ---------------------------------------------------------------- direct kernels
-// One FP32 grid sum: the (axis-aligned) mode table, the grid and the outputs (each may be nullptr).
+// One direct grid sum: the (axis-aligned) mode table, the grid and the outputs (each may be nullptr;
+// y64, k64, mu64 and amp64 are the FP64 form's).
 struct DirectGrid {
     const double* z;    // [dim][n]
     const double* phi;  // [n]
@@ -217,6 +216,11 @@ struct DirectGrid {
     float* y;
     float* k;
     uint8_t* ind;
+    double amp64, mu64;
+    double* y64;
+    double* k64;
+    int64_t mslice;     // modes per slice (blockIdx.z)
+    double* partial64;  // raw sums [slice][nq nx] of the slices, or nullptr
 };
 DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind);
 hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream_t s);
@@ -234,19 +238,8 @@ struct FoldWs {
 FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split);
 hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
                        hipStream_t s);
-// Mode slices of the FP64 grid sum: grids too small to fill the device split the modes
-// into `slices` runs of `mslice` (slices = 1: no split).
-struct ModeSlices {
-    int slices;
-    int64_t mslice;
-};
-ModeSlices direct_grid_f64_slices(const int64_t* gn, int64_t n);
-// `partial` (workspace of direct_grid_f64_slices(gn, n).slices * cells doubles when that is
-// > 1, else unused) receives the slices' raw sums before they are added in slice order.
-hipError_t launch_direct_grid_f64(const double* tx, const double* ty, const double* tz, const double* w, int64_t n,
-                                  int64_t ldp, const int64_t* gn, double amp, const Epi& epi,
-                                  double mu64, float* y, float* k, uint8_t* ind, double* y64,
-                                  double* k64, double* partial, hipStream_t s);
+// `ws` (ws_doubles FP64 values) holds the sums of the mode slices where the launch takes slices.
+hipError_t launch_direct_grid_f64(const DirectGrid& g, const Epi& epi, double* ws, size_t ws_doubles, hipStream_t s);
 // `partial` (workspace, points_mode_slices(P, n) * P floats when that is > 1) receives the
 // per-slice sums when the modes are split across blocks.
 hipError_t launch_direct_points(const double* params, const double* w, int64_t n, int dim, const double* xyz,

@@ -73,8 +73,6 @@ __device__ __forceinline__ void axis_table_rows(const AxisTableArgs a, int64_t i
 
         if constexpr (FMT == TF_REV_F32) {
             st<float>(a.out, e, static_cast<float>(f));
-        } else if constexpr (FMT == TF_REV_F64) {
-            st<double>(a.out, e, f);
         } else if constexpr (FAST && (FMT == TF_CPLX_F32 || FMT == TF_F16 || FMT == TF_BF16)) {
             // one rounding to the table format: the hardware cos/sin of the FP64-reduced
             // fraction in revolutions (|err| ~1e-7) is far below it
@@ -145,7 +143,6 @@ __device__ __forceinline__ void axis_table_block(const AxisTableArgs a, int64_t 
     const int64_t i1 = min(i0 + kTabRows, a.count);
     switch (a.format) {
     case TF_REV_F32: axis_table_rows<TF_REV_F32, true, false>(a, i0, i1, j, az, ps, wj, zero); break;
-    case TF_REV_F64: axis_table_rows<TF_REV_F64, true, false>(a, i0, i1, j, az, ps, wj, zero); break;
     case TF_CPLX_F32: axis_table_rows_t<TF_CPLX_F32>(a, i0, i1, j, az, ps, wj, zero); break;
     case TF_F16: axis_table_rows_t<TF_F16>(a, i0, i1, j, az, ps, wj, zero); break;
     case TF_F16_HILO: axis_table_rows_t<TF_F16_HILO>(a, i0, i1, j, az, ps, wj, zero); break;

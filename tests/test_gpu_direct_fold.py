@@ -1,4 +1,4 @@
-"""GPU parity of the FP32 grid sum's folded contraction at the edges of its tiles: x extents
+"""GPU parity of the direct grid sums' folded contraction at the edges of its tiles: x extents
 around the mirrored column tiles, row counts around the row tiles, mode counts around the
 eight chunks, the 64-mode stages and the matrix steps, with and without weights."""
 import numpy as np
@@ -29,19 +29,21 @@ def _case(orc, grf, shape, n, weighted, seed):
     return z, phi, (np.ones(n) if w is None else w), m, sigma, ell, geo
 
 
+@pytest.mark.parametrize("meth", ["direct_f32", "direct_f64"])
 @pytest.mark.parametrize("weighted", [False, True])
 @pytest.mark.parametrize("shape,n", [((1, 1), 1), ((2, 3), 2), ((3, 1, 1), 7), ((31, 17), 8), ((32, 16), 9),
                                      ((33, 15, 3), 63), ((63, 9, 2), 64), ((64, 4, 4), 65), ((65, 33), 511),
                                      ((300, 41), 513), ((129, 130, 5), 130), ((70, 64, 110), 37)])
-def test_direct_grid_edges(orc, grf, shape, n, weighted):
-    print(f"case direct fold {shape} n={n} weighted={weighted}", flush=True)
+def test_direct_grid_edges(orc, grf, shape, n, weighted, meth):
+    print(f"case direct fold {shape} n={n} weighted={weighted} {meth}", flush=True)
     z, phi, w, m, sigma, ell, geo = _case(orc, grf, shape, n, weighted, 4100 + n)
     C = int(np.prod(shape))
-    out = grf.field_grid(m, shape, method="direct_f32", mu=0.1, thresholds=[0.0], want_k=True, want_ind=True, **geo)
+    out = grf.field_grid(m, shape, method=meth, mu=0.1, thresholds=[0.0], want_k=True, want_ind=True, **geo)
     y = to_np(out["y"])
     cells = np.arange(C) if C <= 20000 else wl.sample_cells(C, 5000, 4200)
     ref = orc.field_points_w(z, phi, w, sigma, ell, orc.grid_centres(shape, **geo)[cells])
-    assert_field(y[cells], ref, sigma, "direct_f32", f"{shape}")
+    scale = sigma * float(np.sqrt(np.mean(w * w)))  # the weighted field's standard deviation
+    assert_field(y[cells], ref, scale, meth, f"{shape}")
     assert np.isfinite(y).all()
     np.testing.assert_array_equal(to_np(out["ind"]), (y > 0.0).astype(np.uint8))
     np.testing.assert_allclose(to_np(out["k"]), np.exp(0.1 + y.astype(np.float64)), rtol=1e-6)
