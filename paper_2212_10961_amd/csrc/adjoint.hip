@@ -376,44 +376,60 @@ void launch_bwd_main(const BwdArgs& a, int64_t chunk, const Geo& geo, bool want_
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ void split_bf16(float v, uint16_t* hi, uint16_t* lo, int64_t e)
-{
-    const __bf16 h = static_cast<__bf16>(v);
-    const __bf16 l = static_cast<__bf16>(v - static_cast<float>(h));
-    hi[e] = __builtin_bit_cast(uint16_t, h);
-    lo[e] = __builtin_bit_cast(uint16_t, l);
-}
+// Operands of one x chunk [x0, x0 + kBwdSepK), made by one launch: blocks [0, ba) the dL/dY
+// rows, the others the x operand.
+struct BwdSepPrep {
+    const float* g;
+    const double* zx;
+    double fs, ox, hx;
+    int64_t n, ldp, nx, x0, ny, nyp, qp, ba;
+    uint16_t *ga_hi, *ga_lo, *ex_hi, *ex_lo;
+};
 
-// dL/dY rows as bf16 hi + lo for the x chunk [x0, x0 + kBwdSepK): row r = z nyp + y (y
-// padded to nyp, a multiple of 32, so that a 32-row tile is one z-slice), cells past nx and
-// padded rows zero.  Stored fragment-major, [r / 32][x / 16][r % 32][x % 16], so that one
-// k-step of a 32-row tile (the A fragment of every lane of a wave) is one contiguous KiB.
-__global__ __launch_bounds__(256) void k_bwd_sep_ga(const float* __restrict__ g, int64_t nx, int64_t x0, int64_t ny,
-                                                   int64_t nyp, int64_t qp, uint16_t* __restrict__ hi,
-                                                   uint16_t* __restrict__ lo)
+// dL/dY rows as bf16 hi + lo: row r = z nyp + y (y padded to nyp, a multiple of 32, so that a
+// 32-row tile is one z-slice), cells past nx and padded rows zero.  Stored fragment-major,
+// [r / 32][x / 16][r % 32][x % 16], so that one k-step of a 32-row tile (the A fragment of every
+// lane of a wave) is one contiguous KiB.  One thread: eight columns of one row.
+__device__ __forceinline__ void bwd_prep_ga(const BwdSepPrep& p, int64_t e)
 {
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= qp * kBwdSepK) return;
-    const int64_t r = e / kBwdSepK, x = e % kBwdSepK;
-    const int64_t z = r / nyp, y = r % nyp;
+    constexpr int kParts = kBwdSepK / 8;
+    const int64_t r = e / kParts;
+    if (r >= p.qp) return;
+    const int64_t x = 8 * (e % kParts);
+    const uint32_t ru = static_cast<uint32_t>(r), ny = static_cast<uint32_t>(p.nyp);  // rows count < 2^31
+    const int64_t z = ru / ny, y = ru % ny;
+    const float* const src = p.g + (z * p.ny + y) * p.nx + p.x0 + x;
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        const float v = y < p.ny && p.x0 + x + m < p.nx ? src[m] : 0.f;
+        const __bf16 h = static_cast<__bf16>(v);
+        const __bf16 l = static_cast<__bf16>(v - static_cast<float>(h));
+        const uint32_t hb = __builtin_bit_cast(uint16_t, h), lb = __builtin_bit_cast(uint16_t, l);
+        if (m & 1) {
+            hi[m >> 1] |= hb << 16;
+            lo[m >> 1] |= lb << 16;
+        } else {
+            hi[m >> 1] = hb;
+            lo[m >> 1] = lb;
+        }
+    }
     const int64_t d = (((r >> 5) * (kBwdSepK / 16) + (x >> 4)) * 32 + (r & 31)) * 16 + (x & 15);
-    split_bf16((y < ny && x0 + x < nx) ? g[(z * ny + y) * nx + x0 + x] : 0.f, hi, lo, d);
+    *reinterpret_cast<uint4*>(p.ga_hi + d) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    *reinterpret_cast<uint4*>(p.ga_lo + d) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 }
 
 // x operand rows 4 j + (Re Ex, Im Ex, x Re Ex, x Im Ex) of the x chunk at x0, at x = ox +
 // (x0 + i + 1/2) hx, phase frac(a_j x) formed and reduced in FP64, then split into bf16 hi +
 // lo; zero for j >= n and x0 + i >= nx.
-__global__ __launch_bounds__(256) void k_bwd_sep_ex(const double* __restrict__ zx, double fs, double ox, double hx,
-                                                   int64_t n, int64_t ldp, int64_t nx, int64_t x0,
-                                                   uint16_t* __restrict__ hi, uint16_t* __restrict__ lo)
+__device__ __forceinline__ void bwd_prep_ex(const BwdSepPrep& p, int64_t e)
 {
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (e >= ldp * kBwdSepK) return;
+    if (e >= p.ldp * kBwdSepK) return;
     const int64_t j = e / kBwdSepK, i = e % kBwdSepK;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (j < n && x0 + i < nx) {
-        const double x = ox + (static_cast<double>(x0 + i) + 0.5) * hx;
-        const double t = zx[j] * fs * x;
+    if (j < p.n && p.x0 + i < p.nx) {
+        const double x = p.ox + (static_cast<double>(p.x0 + i) + 0.5) * p.hx;
+        const double t = p.zx[j] * p.fs * x;
         double sn, cs;
         sincospi(2.0 * (t - floor(t)), &sn, &cs);
         v[0] = cs;
@@ -426,9 +442,18 @@ __global__ __launch_bounds__(256) void k_bwd_sep_ex(const double* __restrict__ z
         const __bf16 h = static_cast<__bf16>(static_cast<float>(v[c]));
         const __bf16 l = static_cast<__bf16>(static_cast<float>(v[c] - static_cast<double>(static_cast<float>(h))));
         const int64_t o = (4 * j + c) * kBwdSepK + i;
-        hi[o] = __builtin_bit_cast(uint16_t, h);
-        lo[o] = __builtin_bit_cast(uint16_t, l);
+        p.ex_hi[o] = __builtin_bit_cast(uint16_t, h);
+        p.ex_lo[o] = __builtin_bit_cast(uint16_t, l);
     }
+}
+
+__global__ __launch_bounds__(256) void k_bwd_sep_prep(BwdSepPrep p)
+{
+    const int64_t b = blockIdx.x;
+    if (b < p.ba)
+        bwd_prep_ga(p, b * 256 + threadIdx.x);
+    else
+        bwd_prep_ex(p, (b - p.ba) * 256 + threadIdx.x);
 }
 
 __device__ __forceinline__ float swap_pair(float v)
@@ -448,9 +473,9 @@ struct BwdSepK {
     float oy, hy, oz, hz;
 };
 
-// Block: 4 waves, 32 modes (8 per wave: columns 4 j + comp of the wave's 32); grid.y splits
+// Block: 4 waves, 32 NG modes (8 NG per wave: NG groups of columns 4 j + comp); grid.y splits
 // the rows.  Each wave keeps its x-operand fragments (all K) in registers and walks 32-row
-// tiles (32 consecutive y of one z-slice): 8 k-steps x 3 bf16 MFMAs, then the epilogue.
+// tiles (32 consecutive y of one z-slice): 8 k-steps x 3 bf16 MFMAs per group, then the epilogue.
 // There the lane of column (j, comp) holds 16 rows of that component and takes the partner
 // component (Re <-> Im) from the neighbouring lane; with e = Ey[y][j] it accumulates its
 // component of V = sum_y U e and of sum_y y U e as own e.x + partner (+-e.y) (the sign by
@@ -458,126 +483,154 @@ struct BwdSepK {
 // comp 0 -> Re(V Ez), comp 1 -> Im(V Ez) (with y and z weights), comp 2 -> Im(V^x Ez).
 // The two half-waves (rows 4h ..) are added at the end.
 // The dL/dY tiles (hi then lo, 8 KiB each per 32 rows) go through LDS, two buffers, loaded
-// straight from global memory (global_load_lds) one tile ahead: the four waves share each
-// tile instead of each fetching it from L2, and the fetch overlaps the previous tile's work.
-typedef const __attribute__((address_space(1))) void bwd_gbl_void;
+// straight from global memory one tile ahead: the four waves share each tile instead of each
+// fetching it from L2, and the fetch overlaps the previous tile's work.
+// Bound by the matrix cores: 128^3 cells x 4096 modes take 193 us, 1.07 PFLOP/s of the 1.25 that a
+// large product reaches here (236 before: a 64-bit division per tile for its slice, and LDS loads
+// that the compiler counted as flat).  With one group the LDS reads of a tile (16 KiB of dL/dY and
+// 8 KiB of Ey per wave) take as long as its 24 MFMAs; two groups share every dL/dY fragment.
 typedef __attribute__((address_space(3))) void bwd_lds_void;
 
-__global__ __launch_bounds__(256) void k_bwd_sep(BwdSepK p, float* __restrict__ partial)
+// 16 bytes per lane from a uniform base plus an unsigned 32-bit byte offset, in the buffer form
+// (a global_load_lds under way would turn the waits for LDS reads into full waits).
+__device__ __forceinline__ void bwd_to_lds(const void* base, uint32_t off, char* s)
+{
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (bwd_lds_void*)s, 16, static_cast<int>(off), 0, 0, 0);
+}
+
+template <int NG>
+__global__ __launch_bounds__(256, NG == 2 ? 2 : 3) void k_bwd_sep(BwdSepK p, float* __restrict__ partial)
 {
     constexpr int kTileB = 32 * kBwdSepK * 2;  // bytes of one 32-row bf16 tile
-    constexpr int kEyOff = 2 * kTileB, kEzOff = kEyOff + 32 * 32 * 8, kBufB = kEzOff + 32 * 8;
+    constexpr int kRowB = 32 * NG * 8;         // bytes of the block's modes in one Ey row
+    constexpr int kEyOff = 2 * kTileB, kEzOff = kEyOff + 32 * kRowB, kBufB = kEzOff + kRowB;
     __shared__ __attribute__((aligned(16))) char sa[2][kBufB];  // A hi, A lo, Ey rows, Ez row
     const int t = threadIdx.x, l = t & 63, h = l >> 5;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int col = l & 31, c = col & 3;
     const float sgn = (c & 1) ? 1.f : -1.f;
-    const int64_t jb = static_cast<int64_t>(blockIdx.x) * 32 + w * 8;
-    const int64_t j = jb + (col >> 2);
+    const int64_t jb0 = static_cast<int64_t>(blockIdx.x) * (32 * NG);
     constexpr int KS = kBwdSepK / 16;
-    uint4 bh[KS], bl[KS];
-    const int64_t brow = (4 * jb + col) * kBwdSepK + 8 * h;
+    uint4 bh[NG][KS], bl[NG][KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        bh[ks] = *reinterpret_cast<const uint4*>(p.ex_hi + brow + 16 * ks);
-        bl[ks] = *reinterpret_cast<const uint4*>(p.ex_lo + brow + 16 * ks);
+    for (int g = 0; g < NG; ++g) {
+        const int64_t brow = (4 * (jb0 + (w * NG + g) * 8) + col) * kBwdSepK + 8 * h;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bh[g][ks] = *reinterpret_cast<const uint4*>(p.ex_hi + brow + 16 * ks);
+            bl[g][ks] = *reinterpret_cast<const uint4*>(p.ex_lo + brow + 16 * ks);
+        }
     }
-    float sIm = 0.f, sRe = 0.f, sY = 0.f, sZ = 0.f;
+    float sIm[NG], sRe[NG], sY[NG], sZ[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) sIm[g] = sRe[g] = sY[g] = sZ[g] = 0.f;
     const int64_t ntile = p.qp / 32;
     const int64_t per = (ntile + gridDim.y - 1) / gridDim.y;
     const int64_t t0 = static_cast<int64_t>(blockIdx.y) * per, t1 = min(ntile, t0 + per);
     // Per tile: 16 chunks of 1 KiB of dL/dY (hi 0..7, lo 8..15), four per wave; the tile's 32
-    // Ey rows of the block's 32 modes (256 B each, four rows per chunk), two chunks per wave;
-    // the Ez row of its slice (256 B, 16 lanes of wave 0).  Lane l moves bytes 16 l .. of a chunk.
-    const int64_t jb0 = static_cast<int64_t>(blockIdx.x) * 32;
-    auto issue = [&](int64_t tile, char* buf) {
+    // Ey rows of the block's modes, 2 NG chunks per wave; the Ez row of its slice (16 NG lanes of
+    // wave 0).  Lane l moves bytes 16 l .. of a chunk.
+    auto issue = [&](int64_t tile, int64_t zt, int64_t yt, char* buf) {
         const char* gh = reinterpret_cast<const char*>(p.ga_hi + tile * 32 * kBwdSepK);
         const char* gl = reinterpret_cast<const char*>(p.ga_lo + tile * 32 * kBwdSepK);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int ch = 4 * w + k;
-            const char* src = (ch < 8 ? gh + ch * 1024 : gl + (ch - 8) * 1024) + 16 * l;
-            __builtin_amdgcn_global_load_lds((bwd_gbl_void*)src, (bwd_lds_void*)(buf + ch * 1024), 16, 0, 0);
+            bwd_to_lds(ch < 8 ? gh + ch * 1024 : gl + (ch - 8) * 1024, 16 * l, buf + ch * 1024);
         }
-        const int64_t zt = tile * 32 / p.nyp, yt = tile * 32 - zt * p.nyp;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int ch = 2 * w + k;
-            const char* src = reinterpret_cast<const char*>(p.ey + (yt + 4 * ch + (l >> 4)) * p.ldp + jb0) + 16 * (l & 15);
-            __builtin_amdgcn_global_load_lds((bwd_gbl_void*)src, (bwd_lds_void*)(buf + kEyOff + ch * 1024), 16, 0, 0);
+        for (int k = 0; k < 2 * NG; ++k) {
+            const int ch = 2 * NG * w + k;
+            constexpr int rows = 1024 / kRowB, lanes = kRowB / 16;  // rows per chunk, lanes per row
+            bwd_to_lds(p.ey + (yt + rows * ch) * p.ldp + jb0,
+                       static_cast<uint32_t>(l / lanes) * static_cast<uint32_t>(p.ldp * 8) + 16 * (l % lanes),
+                       buf + kEyOff + ch * 1024);
         }
-        if (w == 0 && l < 16) {
-            const char* src = reinterpret_cast<const char*>(p.ez + zt * p.ldp + jb0) + 16 * l;
-            __builtin_amdgcn_global_load_lds((bwd_gbl_void*)src, (bwd_lds_void*)(buf + kEzOff), 16, 0, 0);
-        }
+        if (w == 0 && l < kRowB / 16) bwd_to_lds(p.ez + zt * p.ldp + jb0, 16 * l, buf + kEzOff);
     };
-    const int jl = w * 8 + (col >> 2);  // this lane's mode within the block's 32
     const int fo = (col * 16 + 8 * h) * 2;  // this lane's fragment bytes within a k-step's 1 KiB
-    if (t0 < t1) issue(t0, sa[0]);
+    // slice and first row of the tile, stepped along: a 64-bit division per tile costs more scalar
+    // instructions than the tile has vector ones
+    int64_t zi = t0 * 32 / p.nyp, yi = t0 * 32 - zi * p.nyp;
+    if (t0 < t1) issue(t0, zi, yi, sa[0]);
     for (int64_t tile = t0; tile < t1; ++tile) {
         const char* cur = sa[(tile - t0) & 1];
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();  // this tile is in `cur` for every wave; every wave is done with the other buffer
-        if (tile + 1 < t1) issue(tile + 1, sa[(tile + 1 - t0) & 1]);
-        const int64_t q0 = tile * 32;
-        // one accumulator: 128 VGPRs, four waves per SIMD to cover the loads and the epilogue
-        f32x16 acc;
+        const bool wrap = yi + 32 >= p.nyp;
+        const int64_t zn = zi + wrap, yn = wrap ? 0 : yi + 32;
+        if (tile + 1 < t1) issue(tile + 1, zn, yn, sa[(tile + 1 - t0) & 1]);
+        f32x16 acc[NG];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[g][e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            const uint4 ah = *reinterpret_cast<const uint4*>(cur + ks * 1024 + fo);
-            const uint4 al = *reinterpret_cast<const uint4*>(cur + kTileB + ks * 1024 + fo);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bh[ks]),
-                                                          acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bl[ks]),
-                                                          acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, al), __builtin_bit_cast(bf16x8, bh[ks]),
-                                                          acc, 0, 0, 0);
+            const bf16x8 ah = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(cur + ks * 1024 + fo));
+            const bf16x8 al = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(cur + kTileB + ks * 1024 + fo));
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    acc[g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        x == 2 ? al : ah, __builtin_bit_cast(bf16x8, x == 1 ? bl[g][ks] : bh[g][ks]), acc[g], 0, 0, 0);
         }
         // lane holds rows y = y0 + 8 (e / 4) + 4 h + e % 4 of slice zi, column col
-        const int64_t zi = q0 / p.nyp, y0 = q0 - zi * p.nyp + 4 * h;
+        const int64_t y0 = yi + 4 * h;
         const float yb = p.oy + (static_cast<float>(y0) + 0.5f) * p.hy;
-        // Ey of rows 4 h + r of the tile (the y table has nyp rows: padded rows have U = 0)
-        const float2* eyr = reinterpret_cast<const float2*>(cur + kEyOff) + 4 * h * 32 + jl;
-        // sum_y y U e = yb sum U e + hy sum r U e over the lane's rows r
-        float vA = 0.f, vR = 0.f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int r = 8 * (e >> 2) + (e & 3);
-            const float2 ey = eyr[r * 32];
-            const float own = acc[e], oth = swap_pair(own);
-            const float v = fmaf(own, ey.x, oth * (sgn * ey.y));
-            vA += v;
-            vR = fmaf(static_cast<float>(r), v, vR);
-        }
-        const float vY = fmaf(yb, vA, p.hy * vR);
-        const float2 ez = reinterpret_cast<const float2*>(cur + kEzOff)[jl];
         const float zc = p.oz + (static_cast<float>(zi) + 0.5f) * p.hz;
-        const float oA = swap_pair(vA), oY = swap_pair(vY);
-        // (re, im) of V and of sum y U e for this lane's pair
-        const float ra = (c & 1) ? oA : vA, ia = (c & 1) ? vA : oA;
-        const float ry = (c & 1) ? oY : vY, iy = (c & 1) ? vY : oY;
-        const float im = fmaf(ra, ez.y, ia * ez.x);
-        sIm += im;
-        sRe += fmaf(ra, ez.x, -ia * ez.y);
-        sY += fmaf(ry, ez.y, iy * ez.x);
-        sZ = fmaf(zc, im, sZ);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int jl = (w * NG + g) * 8 + (col >> 2);  // this lane's mode within the block's
+            // Ey of rows 4 h + r of the tile (the y table has nyp rows: padded rows have U = 0)
+            const float2* eyr = reinterpret_cast<const float2*>(cur + kEyOff) + 4 * h * (32 * NG) + jl;
+            // sum_y y U e = yb sum U e + hy sum r U e over the lane's rows r
+            float vA = 0.f, vR = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = 8 * (e >> 2) + (e & 3);
+                const float2 ey = eyr[r * 32 * NG];
+                const float own = acc[g][e], oth = swap_pair(own);
+                const float v = fmaf(own, ey.x, oth * (sgn * ey.y));
+                vA += v;
+                vR = fmaf(static_cast<float>(r), v, vR);
+            }
+            const float vY = fmaf(yb, vA, p.hy * vR);
+            const float2 ez = reinterpret_cast<const float2*>(cur + kEzOff)[jl];
+            const float oA = swap_pair(vA), oY = swap_pair(vY);
+            // (re, im) of V and of sum y U e for this lane's pair
+            const float ra = (c & 1) ? oA : vA, ia = (c & 1) ? vA : oA;
+            const float ry = (c & 1) ? oY : vY, iy = (c & 1) ? vY : oY;
+            const float im = fmaf(ra, ez.y, ia * ez.x);
+            sIm[g] += im;
+            sRe[g] += fmaf(ra, ez.x, -ia * ez.y);
+            sY[g] += fmaf(ry, ez.y, iy * ez.x);
+            sZ[g] = fmaf(zc, im, sZ[g]);
+        }
+        zi = zn;
+        yi = yn;
     }
-    sIm += __shfl_xor(sIm, 32);
-    sRe += __shfl_xor(sRe, 32);
-    sY += __shfl_xor(sY, 32);
-    sZ += __shfl_xor(sZ, 32);
-    if (h == 0) {
-        float* out = partial + static_cast<int64_t>(blockIdx.y) * 5 * p.ldp;
-        if (c == 1) {
-            out[j] = sIm;
-            out[2 * p.ldp + j] = sY;
-            out[3 * p.ldp + j] = sZ;
-        } else if (c == 0) {
-            out[4 * p.ldp + j] = sRe;
-        } else if (c == 2) {
-            out[p.ldp + j] = sIm;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const int64_t j = jb0 + (w * NG + g) * 8 + (col >> 2);
+        sIm[g] += __shfl_xor(sIm[g], 32);
+        sRe[g] += __shfl_xor(sRe[g], 32);
+        sY[g] += __shfl_xor(sY[g], 32);
+        sZ[g] += __shfl_xor(sZ[g], 32);
+        if (h == 0) {
+            float* out = partial + static_cast<int64_t>(blockIdx.y) * 5 * p.ldp;
+            if (c == 1) {
+                out[j] = sIm[g];
+                out[2 * p.ldp + j] = sY[g];
+                out[3 * p.ldp + j] = sZ[g];
+            } else if (c == 0) {
+                out[4 * p.ldp + j] = sRe[g];
+            } else if (c == 2) {
+                out[p.ldp + j] = sIm[g];
+            }
         }
     }
 }
@@ -623,7 +676,9 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s)
         // hold one chunk); chunk xc writes its row-chunk sums to partial slots
         // [xc chunks, (xc + 1) chunks), and the reduction adds every slot
         const BwdSep& b = *a.sep;
-        const int64_t ng = b.qp * kBwdSepK, ne = a.ldp * kBwdSepK;
+        const int64_t ne = a.ldp * kBwdSepK;
+        BwdSepPrep prep{a.gy, b.zx, b.fsx, a.go[0], a.gh[0], a.n, a.ldp, a.gn[0], 0, b.ny, b.nyp, b.qp,
+                        (b.qp * (kBwdSepK / 8) + 255) / 256, b.ga_hi, b.ga_lo, b.ex_hi, b.ex_lo};
         const int64_t nxc = (a.gn[0] + kBwdSepK - 1) / kBwdSepK;
         BwdSepK k{b.ga_hi, b.ga_lo, b.ex_hi, b.ex_lo, b.ey, b.ez, a.ldp, b.qp, b.ny, b.nyp,
                   static_cast<float>(geo.oy), static_cast<float>(geo.hy), static_cast<float>(geo.oz),
@@ -632,15 +687,21 @@ hipError_t launch_backward(const BwdArgs& a, hipStream_t s)
             k.oz = 0.f;
             k.hz = 0.f;
         }
+        // two mode groups per wave (k_bwd_sep) where a block walks at least four tiles: the whole
+        // call 224.8 us for 229.5 with one at 128^3 x 4096 modes (32 tiles), 85.0 for 86.0 at 96^3 x
+        // 2000 (9 tiles); with fewer the start of a block costs more (46.5 for 43.4 at 100 x 70 x 33
+        // x 1000 and 66.9 for 65.6 at 128^3 x 500, 2 tiles each)
+        const bool two = b.qp / 32 >= 4 * b.chunks;  // a.ldp is a multiple of 64
         for (int64_t xc = 0; xc < nxc; ++xc) {
             const int64_t x0 = xc * kBwdSepK;
-            hipLaunchKernelGGL(k_bwd_sep_ga, dim3(static_cast<unsigned>((ng + 255) / 256)), dim3(256), 0, s, a.gy,
-                               a.gn[0], x0, b.ny, b.nyp, b.qp, b.ga_hi, b.ga_lo);
-            hipLaunchKernelGGL(k_bwd_sep_ex, dim3(static_cast<unsigned>((ne + 255) / 256)), dim3(256), 0, s, b.zx,
-                               b.fsx, a.go[0], a.gh[0], a.n, a.ldp, a.gn[0], x0, b.ex_hi, b.ex_lo);
+            prep.x0 = x0;
+            hipLaunchKernelGGL(k_bwd_sep_prep, dim3(static_cast<unsigned>(prep.ba + (ne + 255) / 256)), dim3(256), 0, s,
+                               prep);
             if (xc == 0) timer_mark(s, true);
-            hipLaunchKernelGGL(k_bwd_sep, dim3(static_cast<unsigned>(a.ldp / 32), static_cast<unsigned>(b.chunks)),
-                               dim3(256), 0, s, k, a.partial + xc * b.chunks * 5 * a.ldp);
+            const unsigned modes = two ? 64 : 32;
+            hipLaunchKernelGGL((two ? k_bwd_sep<2> : k_bwd_sep<1>),
+                               dim3(static_cast<unsigned>(a.ldp) / modes, static_cast<unsigned>(b.chunks)), dim3(256), 0,
+                               s, k, a.partial + xc * b.chunks * 5 * a.ldp);
         }
     } else if (grid && a.tx) {
         timer_mark(s, true);

@@ -1023,7 +1023,7 @@ static int backward_common(const char* fn, const grf_modes* modes, const double*
     float* scal = c.take<float>(bwd_scal_floats(modes->n));
     grf_modes am;  // sums run on k itself; grad_ell maps back through the original table
     GRF_HIP(aligned_modes(modes, kbuf, s, &am));
-    GRF_HIP(launch_mode_params(am.z, am.phi, am.dim, am.n, ldp, am.ell, params, s));
+    if (!sep) GRF_HIP(launch_mode_params(am.z, am.phi, am.dim, am.n, ldp, am.ell, params, s));
     GridWs tabs;
     BwdSep bs{};
     if (sep) {
