@@ -590,6 +590,15 @@ def grad_z_from_k(modes: Modes, grad_k: torch.Tensor, out: Optional[torch.Tensor
     return gz
 
 
+def _host_values(sigma, ell):
+    """(sigma, [ell]) as Python floats, by one copy from the device where the two lie together."""
+    sigma, ell = sigma.detach(), ell.detach()
+    if sigma.device == ell.device and sigma.dtype == ell.dtype and sigma.numel() == 1 and ell.dim() == 1:
+        v = torch.cat([sigma.reshape(1), ell]).tolist()
+        return v[0], v[1:]
+    return float(sigma), [float(v) for v in ell.cpu()]
+
+
 class GRFPoints(torch.autograd.Function):
     """Y at fixed points as a differentiable function of (phi, z, sigma, ell).
 
@@ -600,18 +609,21 @@ class GRFPoints(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, phi, z, sigma, ell, xyz, rot=None):
-        modes = Modes(z.detach().contiguous(), phi.detach().contiguous(), float(sigma),
-                      [float(v) for v in ell.detach().cpu()], None if rot is None else np.asarray(rot, float))
+        s, l = _host_values(sigma, ell)
+        modes = Modes(z.detach().contiguous(), phi.detach().contiguous(), s, l,
+                      None if rot is None else np.asarray(rot, float))
         y = field_points(modes, xyz, method="direct_f32")["y"]
         ctx.save_for_backward(phi, z, sigma, ell, xyz, y)
         ctx.rot = modes.rot
+        # backward takes sigma and ell from here: reading them off the device again would stop the
+        # host twice between the loss and the adjoint
+        ctx.host = s, l
         return y
 
     @staticmethod
     def backward(ctx, gy):
         phi, z, sigma, ell, xyz, y = ctx.saved_tensors
-        modes = Modes(z.detach().contiguous(), phi.detach().contiguous(), float(sigma),
-                      [float(v) for v in ell.detach().cpu()], ctx.rot)
+        modes = Modes(z.detach().contiguous(), phi.detach().contiguous(), *ctx.host, ctx.rot)
         g = field_backward(modes, xyz, gy.detach().to(torch.float32).contiguous(), y_saved=y)
         dz = grad_z_from_k(modes, g["dk"])  # k = rot diag(1/ell) z: dL/dz = diag(1/ell) rot^T dL/dk
         return (g["dphi"].to(phi.dtype), dz.to(z.dtype), g["dsigma"].reshape(()).to(sigma.dtype),
