@@ -569,7 +569,12 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
         const SepArgs s2 = sep_args(&a2, grid, method, -1, Epi{}, f2, nullptr, nullptr, w2);
         SepArgs s1 = sep_args(&a1, grid, method, -1, Epi{}, f1, nullptr, nullptr, w1);
         s1.timed = true;
-        GRF_HIP(launch_sep_pair(s1, &s2, s));
+        GRF_HIP(launch_sep_pair(s1, &s2, s, false));
+        if (s1.partial) {
+            GRF_HIP(launch_pluri_slices(s1.partial, s2.partial, s1.slices, C, s1.amp, s2.amp, make_pluri(rule, rt),
+                                        facies, value, y1, y2, s));
+            return GRF_OK;
+        }
     } else {
         if ((rc = grid_launch(&a1, grid, method, -1, Epi{}, f1, nullptr, nullptr, tabs, s))) return rc;
         if ((rc = grid_launch(&a2, grid, method, -1, Epi{}, f2, nullptr, nullptr, tabs, s))) return rc;

@@ -314,12 +314,8 @@ __global__ __launch_bounds__(kDgWaves * 64) void k_direct_batch(const DirectBatc
 }
 
 // ---------------------------------------------------------------------------- points
-__global__ __launch_bounds__(256) void k_points_reduce(const float* __restrict__ partial, int slices, int64_t P,
-                                                      float amp, Epi epi, float* __restrict__ y,
-                                                      float* __restrict__ k, uint8_t* __restrict__ ind)
+__device__ __forceinline__ float slice_sum(const float* __restrict__ partial, int slices, int64_t P, int64_t p)
 {
-    const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (p >= P) return;
     // Sixteen slice loads are in flight at a time; the adds keep slice order.
     constexpr int kGroup = 16;
     float s = 0.f;
@@ -332,7 +328,16 @@ __global__ __launch_bounds__(256) void k_points_reduce(const float* __restrict__
         for (int u = 0; u < kGroup; ++u) s += v[u];
     }
     for (; q < slices; ++q) s += partial[static_cast<int64_t>(q) * P + p];
-    store_out(p, amp * s, epi, y, k, ind);
+    return s;
+}
+
+__global__ __launch_bounds__(256) void k_points_reduce(const float* __restrict__ partial, int slices, int64_t P,
+                                                      float amp, Epi epi, float* __restrict__ y,
+                                                      float* __restrict__ k, uint8_t* __restrict__ ind)
+{
+    const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (p >= P) return;
+    store_out(p, amp * slice_sum(partial, slices, P, p), epi, y, k, ind);
 }
 
 // Each lane owns R points; every mode's (a_x, a_y, a_z, psi) in revolutions is
@@ -486,6 +491,25 @@ __global__ __launch_bounds__(256) void k_pluri4(const float* __restrict__ y1, co
         if (facies) facies[c] = static_cast<uint8_t>(f);
         if (value) value[c] = pe.values[f];
     }
+}
+
+// The rule straight from both fields' slice sums (the order and rounding of k_points_reduce), the
+// fields stored only where the caller keeps them: one pass over the sums in place of three launches.
+// Bound by its launch and one pass over the sums: 5.7 us at 1024 x 512 cells against 4.75 + 4.75 +
+// 4.35 us for the three, the whole call 64 -> 58 us.
+__global__ __launch_bounds__(256) void k_pluri_slices(const float* __restrict__ p1, const float* __restrict__ p2,
+                                                     int slices, int64_t n, float amp1, float amp2, PluriEpi pe,
+                                                     uint8_t* __restrict__ facies, float* __restrict__ value,
+                                                     float* __restrict__ y1, float* __restrict__ y2)
+{
+    const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const float a = amp1 * slice_sum(p1, slices, n, c), b = amp2 * slice_sum(p2, slices, n, c);
+    const int f = pluri_facies(a, b, pe);
+    if (y1) y1[c] = a;
+    if (y2) y2[c] = b;
+    if (facies) facies[c] = static_cast<uint8_t>(f);
+    if (value) value[c] = pe.values[f];
 }
 
 // One cell per thread and step (unaligned buffers).
@@ -644,6 +668,15 @@ int direct_batch_blocks_per_cu()
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_direct_batch, kDgWaves * 64, 0) != hipSuccess) return 1;
     return nb > 0 ? nb : 1;
+}
+
+hipError_t launch_pluri_slices(const float* p1, const float* p2, int slices, int64_t n, float amp1, float amp2,
+                               const PluriEpi& pe, uint8_t* facies, float* value, float* y1, float* y2, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pluri_slices, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, p1, p2, slices, n,
+                       amp1, amp2, pe, facies, value, y1, y2);
+    return hipGetLastError();
 }
 
 hipError_t launch_pluri_epilogue(const float* y1, const float* y2, int64_t n, const PluriEpi& pe, uint8_t* facies,

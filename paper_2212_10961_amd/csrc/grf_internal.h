@@ -97,6 +97,9 @@ struct PluriEpi {
 // Device copy of a rule's lookup tables (bin -> facies bytes, then the facies values).
 constexpr size_t kRuleBytes = 256 + sizeof(float) * GRF_MAX_FACIES;
 hipError_t launch_rule_tables(const grf_trunc2& r, void* dst, hipStream_t s);
+// The same from both fields' mode-slice sums (slices x n each); y1, y2 optional.
+hipError_t launch_pluri_slices(const float* p1, const float* p2, int slices, int64_t n, float amp1, float amp2,
+                               const PluriEpi& pe, uint8_t* facies, float* value, float* y1, float* y2, hipStream_t s);
 hipError_t launch_pluri_epilogue(const float* y1, const float* y2, int64_t n, const PluriEpi& pe, uint8_t* facies,
                                  float* value, hipStream_t s);
 
@@ -323,8 +326,9 @@ struct SepArgs {
 };
 hipError_t launch_sep(const SepArgs& a, hipStream_t s);
 // Two fields on the same grid (same method, sizes and ldp; the epilogue parameters of `a`
-// apply to both) in one launch; b may be nullptr.
-hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s);
+// apply to both) in one launch; b may be nullptr.  add = false leaves the slice sums of a mode
+// split in `partial`.
+hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s, bool add = true);
 int sep_tile_count();                // number of tile selectors
 void sep_tile_shape(int tile, int* bm, int* bn);
 int sep_tile_slices(int tile, int method, bool d3);  // z-slices per block

@@ -1201,7 +1201,7 @@ int sep_batch_blocks_per_cu(int method, bool d3)
 
 hipError_t launch_sep(const SepArgs& a, hipStream_t s) { return launch_sep_pair(a, nullptr, s); }
 
-hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s)
+hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s, bool add)
 {
     int tile = a.tile < 0 ? sep_default_tile(a.method, a.nx, a.ny, a.nz) : a.tile;
     if (tile >= sep_tile_count()) return hipErrorInvalidValue;
@@ -1213,7 +1213,7 @@ hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s)
     if (split && (a.tile >= 0 || a.slices < 1 || a.pairs < 1 || (b && b->partial == nullptr) ||
                   static_cast<int64_t>(a.slices) * a.pairs * 2 * kJC < a.ldp))
         return hipErrorInvalidValue;
-    TimedScope timed(s, split && a.timed);  // the contraction and the slice sums
+    TimedScope timed(s, split && a.timed);  // the contraction and, if added here, the slice sums
     hipError_t e;
     switch (a.method) {
     case GRF_SEP_BF16: e = launch_d<true, false>(a, b, tile, s); break;
@@ -1222,7 +1222,7 @@ hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s)
     case GRF_SEP_F16_X3: e = launch_d<false, true>(a, b, tile, s); break;
     default: return hipErrorInvalidValue;
     }
-    if (e != hipSuccess || !split) return e;
+    if (e != hipSuccess || !split || !add) return e;
     const int64_t C = a.nx * a.ny * a.nz;
     e = launch_points_reduce(a.partial, a.slices, C, a.amp, a.epi, a.y, a.k, a.ind, s);
     if (e == hipSuccess && b) e = launch_points_reduce(b->partial, a.slices, C, b->amp, a.epi, b->y, b->k, b->ind, s);
