@@ -29,10 +29,11 @@ sys.path.insert(0, str(ROOT))
 METRIC = "mode·cell evals/s: FP32 direct sum vs MFMA separable at rel-RMS≤1e-3"
 HBM_PEAK = 8.0e12            # B/s
 MFMA_F16_PEAK = 2.5e15       # dense fp16/bf16 flop/s
-# ALU roofline of the direct sums: 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz = 3.93e13 lane-ops/s;
-# v_cos_f32 issues at half rate on gfx950 and every mode-point needs one cosine; on grids every
-# mode-cell is two full-rate FMAs (the angle sum of the x and (y,z) phases): the same peak.
+# ALU roofline of the point sums: 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz = 3.93e13 lane-ops/s;
+# v_cos_f32 issues at half rate on gfx950 and every mode-point needs one cosine.
 COS_PEAK = 256 * 4 * 16 * 2.4e9 / 2.0
+# Direct grid sums: 2 flops per mode-cell on the FP32 matrix cores (64 flops per cycle and SIMD).
+MFMA_F32_PEAK = 256 * 4 * 64 * 2.4e9
 
 
 def log(msg):
@@ -254,18 +255,21 @@ def main():
     head = min(ok, key=lambda m: results[m]["ms_per_step"]) if ok else methods[0]
     r = results[head]
     passes = 3 if head.endswith("x3") else 1
-    flops = 4.0 * N * C * passes if head.startswith("sep") else None
-    src = ROOT / "paper_2212_10961_amd" / "csrc" / ("sep.hip" if head.startswith("sep") else "direct.hip")
+    per = 2 if head.endswith("x3") else 4  # the hi+lo forms are folded over the grid's middle
+    flops = float(per) * N * C * passes if head.startswith("sep") else None
+    name = "k_fold" if head.endswith("x3") else "k_sep"
+    src = ROOT / "paper_2212_10961_amd" / "csrc" / (
+        "direct.hip" if not flops else "fold.hip" if name == "k_fold" else "sep.hip")
     if flops:
         achieved = flops / (r["kernel_ms"] * 1e-3)
         roof = {"bound": "mfma", "achieved": achieved / 1e12, "peak": MFMA_F16_PEAK / 1e12, "unit": "TFLOP/s",
                 "frac": achieved / MFMA_F16_PEAK, "traffic": read_traffic(f"{head}_grid3d_256_exp", src),
-                "kernel": f"k_sep ({head})", "kernel_ms": r["kernel_ms"],
-                "algorithmic": f"4 flop per mode-cell per pass x {N} modes x {C} cells x {passes} pass"}
+                "kernel": f"{name} ({head})", "kernel_ms": r["kernel_ms"],
+                "algorithmic": f"{per} flop per mode-cell per pass x {N} modes x {C} cells x {passes} pass"}
     else:
-        achieved = N * C / (r["kernel_ms"] * 1e-3)
-        roof = {"bound": "alu", "achieved": achieved, "peak": COS_PEAK, "unit": "mode·cell/s",
-                "frac": achieved / COS_PEAK, "traffic": None, "kernel": "k_direct_grid", "kernel_ms": r["kernel_ms"]}
+        achieved = 2.0 * N * C / (r["kernel_ms"] * 1e-3)
+        roof = {"bound": "mfma_f32", "achieved": achieved / 1e12, "peak": MFMA_F32_PEAK / 1e12, "unit": "TFLOP/s",
+                "frac": achieved / MFMA_F32_PEAK, "traffic": None, "kernel": "k_direct_grid", "kernel_ms": r["kernel_ms"]}
 
     line = {
         "metric": METRIC, "value": r["mode_cells_per_s"], "unit": "mode·cell/s", "n_gpus": 1,
@@ -285,9 +289,9 @@ def main():
     if "direct_f32" in results:
         d = results["direct_f32"]
         line["direct_f32"] = {"mode_cells_per_s": d["mode_cells_per_s"], "ms_per_step": d["ms_per_step"],
-                              "roofline": {"bound": "alu", "achieved": N * C / (d["kernel_ms"] * 1e-3),
-                                           "peak": COS_PEAK, "unit": "mode·cell/s",
-                                           "frac": N * C / (d["kernel_ms"] * 1e-3) / COS_PEAK},
+                              "roofline": {"bound": "mfma_f32", "achieved": 2.0 * N * C / (d["kernel_ms"] * 1e-3) / 1e12,
+                                           "peak": MFMA_F32_PEAK / 1e12, "unit": "TFLOP/s",
+                                           "frac": 2.0 * N * C / (d["kernel_ms"] * 1e-3) / MFMA_F32_PEAK},
                               "speedup_of_headline": d["ms_per_step"] / r["ms_per_step"]}
 
     if not args.no_extras and not args.only:
