@@ -107,7 +107,8 @@ struct FoldTabs {
     int64_t bb, by;  // thread blocks of the column and y tables
 };
 
-// One thread: eight modes of one point of one axis (64 contiguous bytes); blockIdx.y = octet.
+// One thread: eight modes of one point of one axis (64 contiguous bytes), for the octets blockIdx.y,
+// blockIdx.y + gridDim.y .. (more octets than gridDim.y can count: tables of 2^19 modes and more).
 // Columns, and the rows of a 2-D grid, are stored split; y and z of a 3-D grid as FP32.
 template <bool BF>
 __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
@@ -119,42 +120,44 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
     const int64_t rows = axis == 0 ? a.half : (axis == 1 ? a.ny : a.nz);
     const int64_t i = b * 256 + threadIdx.x;
     if (i >= rows) return;
-    const int64_t oct = blockIdx.y;
     const double* const z = a.z + axis * a.n;
     const double xc = a.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
     const double x = axis == 0 ? a.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
                      : axis == 1 ? a.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
                                  : a.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
-    float c[8], s[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        const int64_t j = oct * 8 + m;
-        c[m] = s[m] = 0.f;  // modes past n add nothing
-        if (j < a.n) {
-            double t = z[j] * x;
-            if (axis == 1) t += fma(a.z[j], xc, a.phi[j] * kInvTwoPi);
-            double sd, cd;
-            sincospi(2.0 * __builtin_amdgcn_fract(t), &sd, &cd);
-            const double w = axis == 1 && a.w ? a.w[j] : 1.0;
-            c[m] = static_cast<float>(w * cd);
-            s[m] = static_cast<float>(w * sd);
-        }
-    }
     const bool split = axis == 0 || (axis == 1 && a.nz == 0);
-    uint4 o[4];
-    if (split) {
-        split8<BF>(c, o[0], o[1]);
-        split8<BF>(s, o[2], o[3]);
-    } else {
-        o[0] = __builtin_bit_cast(uint4, make_float4(c[0], c[1], c[2], c[3]));
-        o[1] = __builtin_bit_cast(uint4, make_float4(c[4], c[5], c[6], c[7]));
-        o[2] = __builtin_bit_cast(uint4, make_float4(s[0], s[1], s[2], s[3]));
-        o[3] = __builtin_bit_cast(uint4, make_float4(s[4], s[5], s[6], s[7]));
-    }
-    uint4* const out = (axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz)) + oct * rows * 4 + (split ? i * 4 : (axis == 1 ? i : i * 4));
+    uint4* const base = (axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz)) + (split || axis == 2 ? i * 4 : i);
     const int64_t step = !split && axis == 1 ? rows : 1;
+    for (int64_t oct = blockIdx.y; oct < a.ldp / 8; oct += gridDim.y) {
+        float c[8], s[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) out[q * step] = o[q];
+        for (int m = 0; m < 8; ++m) {
+            const int64_t j = oct * 8 + m;
+            c[m] = s[m] = 0.f;  // modes past n add nothing
+            if (j < a.n) {
+                double t = z[j] * x;
+                if (axis == 1) t += fma(a.z[j], xc, a.phi[j] * kInvTwoPi);
+                double sd, cd;
+                sincospi(2.0 * __builtin_amdgcn_fract(t), &sd, &cd);
+                const double w = axis == 1 && a.w ? a.w[j] : 1.0;
+                c[m] = static_cast<float>(w * cd);
+                s[m] = static_cast<float>(w * sd);
+            }
+        }
+        uint4 o[4];
+        if (split) {
+            split8<BF>(c, o[0], o[1]);
+            split8<BF>(s, o[2], o[3]);
+        } else {
+            o[0] = __builtin_bit_cast(uint4, make_float4(c[0], c[1], c[2], c[3]));
+            o[1] = __builtin_bit_cast(uint4, make_float4(c[4], c[5], c[6], c[7]));
+            o[2] = __builtin_bit_cast(uint4, make_float4(s[0], s[1], s[2], s[3]));
+            o[3] = __builtin_bit_cast(uint4, make_float4(s[4], s[5], s[6], s[7]));
+        }
+        uint4* const out = base + oct * rows * 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q * step] = o[q];
+    }
 }
 
 struct FoldArgs {
@@ -557,9 +560,8 @@ hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi
     t.tz = t.nz ? reinterpret_cast<uint4*>(base + w.tz) : nullptr;
     t.bb = (t.half + 255) / 256;
     t.by = (t.ny + 255) / 256;
-    const int64_t tb = t.bb + t.by + (t.nz + 255) / 256, oct = ldp / 8;
-    if (tb > 0x7fffffff || oct > 65535) return hipErrorInvalidValue;
-    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(oct));
+    const int64_t tb = t.bb + t.by + (t.nz + 255) / 256;  // axes are at most 2^24 long
+    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(std::min<int64_t>(ldp / 8, 65535)));
     if (bf) hipLaunchKernelGGL(k_fold_tables<true>, tg, dim3(256), 0, s, t);
     else hipLaunchKernelGGL(k_fold_tables<false>, tg, dim3(256), 0, s, t);
     hipError_t e = hipGetLastError();
