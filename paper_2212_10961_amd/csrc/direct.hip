@@ -541,7 +541,8 @@ hipError_t launch_direct_tile(const DirectGrid& g, const Epi& epi, hipStream_t s
     const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2;
     const int64_t ti = (half + TS - 1) / TS, tq = (g.nq + TI * TS - 1) / (TI * TS);
     const int64_t tiles = ti * tq;
-    const int64_t gy = (tiles + 0x3fffffff) / 0x40000000;  // grids of more than 2^30 tiles fold into y
+    // more threads along x than 32 bits count are silently dropped: more tiles fold into y
+    const int64_t gy = (tiles + kMaxGridX - 1) / kMaxGridX;
     if (gy > 65535) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>((tiles + gy - 1) / gy), static_cast<unsigned>(gy), static_cast<unsigned>(slices));
     if (g.w)

@@ -225,8 +225,9 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
     const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     // Consecutive blocks run on different XCDs, each with its own L2: every XCD takes a run of
     // consecutive work items (slice by slice, columns fastest), whose blocks read the same table
-    // stages at the same time.
-    const int64_t item = static_cast<int64_t>(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    // stages at the same time.  (gridDim.x is a multiple of 8.)
+    const int64_t bid = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    const int64_t item = (bid & 7) * (static_cast<int64_t>(gridDim.y) * (gridDim.x >> 3)) + (bid >> 3);
     if (item >= a.items) return;  // the whole block
     const int64_t slice = item / a.tiles, tile = item - slice * a.tiles;
     const int64_t i0 = tile % a.tiles_i * BN, q0 = tile / a.tiles_i * BM;
@@ -496,9 +497,9 @@ hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, 
     a.tiles_i = (a.half + 64 * TN - 1) / (64 * TN);
     a.tiles = a.tiles_i * ((a.nq + 64 * TM - 1) / (64 * TM));
     a.items = a.tiles * slices;
-    const int64_t blocks = (a.items + 7) / 8 * 8;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 g(static_cast<unsigned>(blocks)), b(512);
+    const int64_t gy = (a.items + kMaxGridX - 1) / kMaxGridX;
+    if (gy > 65535) return hipErrorInvalidValue;
+    const dim3 g(static_cast<unsigned>((((a.items + gy - 1) / gy) + 7) / 8 * 8), static_cast<unsigned>(gy)), b(512);
     if (a.tz) {
         if (bf) hipLaunchKernelGGL((k_fold<TM, TN, true, true>), g, b, 0, s, a, epi);
         else hipLaunchKernelGGL((k_fold<TM, TN, false, true>), g, b, 0, s, a, epi);

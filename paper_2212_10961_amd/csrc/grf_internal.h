@@ -111,6 +111,10 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // mode chunks of the kernels never straddle the end of a row).
 inline int64_t padded_modes(int64_t n) { return round_up(n, 64); }
 
+// Most blocks of 512 threads along a launch's first dimension: 2^32 threads and more there are
+// silently dropped.  (A multiple of 8.)
+constexpr int64_t kMaxGridX = int64_t(1) << 22;
+
 // Bump allocator over a caller workspace.
 struct Carve {
     char* base;
