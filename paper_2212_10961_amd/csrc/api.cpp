@@ -176,9 +176,16 @@ static int resolve_grid_method(int method, const grf_grid* g)
     return method;
 }
 
+// Whether a method's default evaluation on this grid is the folded contraction (fold.hip).
+static bool folds(const grf_modes* m, const grf_grid* g, int method)
+{
+    return is_hilo(method) && fold_default(is_bf16(method), m->dim, g->n[0], g->n[1], g->n[2], m->n);
+}
+
 GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
 {
     GridWs w;
+    const bool fold = folds(m, g, method);
     Carve c(base);
     const int64_t ldp = padded_modes(m->n);
     const int dim = m->dim;
@@ -200,16 +207,16 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
         w.t[1] = c.take<uint32_t>(size_t(g->n[1]) * ldp);
         if (hilo) w.tlo[1] = c.take<uint32_t>(size_t(g->n[1]) * ldp);
         // grids of few tiles: the modes split over slices whose sums are added afterwards
-        w.slices = sep_mode_slices(method, dim, g->n[0], g->n[1], g->n[2], ldp, &w.pairs);
+        if (!fold) w.slices = sep_mode_slices(method, dim, g->n[0], g->n[1], g->n[2], ldp, &w.pairs);
         if (w.slices > 1) {
             const size_t before = c.used;
             w.partial = c.take<float>(size_t(w.slices) * size_t(g->n[0] * g->n[1] * g->n[2]));
             w.split_bytes = c.used - before;
         }
     }
-    // the hi+lo forms' default evaluation (fold.hip) keeps its tables, never larger than the ones
-    // above, and its slice sums here instead
-    if (is_hilo(method)) {
+    // the folded evaluation keeps its tables, never larger than the ones above (which explicit tiles
+    // take), and its slice sums here instead
+    if (fold) {
         const FoldWs f = fold_ws(g->n[0], g->n[1], g->n[2], ldp, dim, true);
         const size_t tables = c.used;
         c.used = std::max(c.used, f.partial + f.split_bytes);
@@ -398,6 +405,11 @@ static SepArgs sep_args(const grf_modes* modes, const grf_grid* grid, int method
 static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method, int tile, const Epi& e, float* y,
                        float* k, uint8_t* ind, void* ws, hipStream_t s, bool allow_split = true)
 {
+    if (tile < 0 && folds(modes, grid, method)) {
+        GRF_HIP(launch_fold(direct_grid_args(modes, grid, y, k, ind), padded_modes(modes->n), is_bf16(method), e, ws,
+                            allow_split, true, s));
+        return GRF_OK;
+    }
     GridWs w = grid_ws(modes, grid, method, ws);
     if (!allow_split && w.split_bytes) w.partial = nullptr;  // the workspace holds the tables only
     if (!is_sep(method)) {  // operands are formed on chip: no tables
@@ -406,11 +418,6 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
         GRF_HIP(method == GRF_DIRECT_F32
                     ? launch_direct_grid_f32(d, e, s)
                     : launch_direct_grid_f64(d, e, static_cast<double*>(ws), w.bytes / sizeof(double), s));
-        return GRF_OK;
-    }
-    if (is_hilo(method) && tile < 0) {
-        GRF_HIP(launch_fold(direct_grid_args(modes, grid, y, k, ind), padded_modes(modes->n), is_bf16(method), e, ws,
-                            allow_split, true, s));
         return GRF_OK;
     }
     GRF_HIP(build_tables(modes, grid, method, w, s));
@@ -506,9 +513,9 @@ static size_t pluri_grid_ws(const grf_modes* m1, const grf_modes* m2, const grf_
                             bool own_y2)
 {
     const int64_t C = g->n[0] * g->n[1] * g->n[2];
-    // one-pass separable forms: both fields' tables at once (one table launch, one contraction)
+    // separable forms: both fields' tables at once (one table launch, one contraction)
     const size_t b1 = grid_ws(m1, g, method, nullptr).bytes, b2 = grid_ws(m2, g, method, nullptr).bytes;
-    const size_t t = is_sep(method) && !is_hilo(method) ? b1 + b2 : std::max(b1, b2);
+    const size_t t = is_sep(method) ? b1 + b2 : std::max(b1, b2);
     const size_t f = align256(sizeof(float) * size_t(C));
     return align256(kRuleBytes) + rot_ws_bytes(m1) + rot_ws_bytes(m2) + (own_y1 ? f : 0) + (own_y2 ? f : 0) + t;
 }
@@ -558,7 +565,9 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
     GRF_HIP(aligned_modes(m1, k1, s, &a1));
     GRF_HIP(aligned_modes(m2, k2, s, &a2));
     GRF_HIP(launch_rule_tables(*rule, rt, s));
-    if (is_sep(method) && !is_hilo(method)) {
+    // (hi+lo tables of different padded lengths run one after the other)
+    if (is_sep(method) && !folds(&a1, grid, method) && !folds(&a2, grid, method) &&
+        (!is_hilo(method) || padded_modes(a1.n) == padded_modes(a2.n))) {
         // both fields: one launch of the six (2-D: four) tables, one of the contraction
         const GridWs w1 = grid_ws(&a1, grid, method, tabs);
         const GridWs w2 = grid_ws(&a2, grid, method, static_cast<char*>(tabs) + w1.bytes);

@@ -21,17 +21,21 @@
 // of between them, and the matrix waves, whose next fragments are always ready, read half a
 // stage ahead.
 //
-// What bounds it: 256^3 x 4,096 modes take 0.44 ms; the same kernel without the row products' vector
-// work takes 0.35 ms, where the matrix cores are busy 73% of the cycles at the 1.6 GHz that the
-// chip holds under this load (1.2 PFLOP/s, the rate of a large library product).  One barrier for
+// What bounds it: 256^3 x 4,096 modes take 0.36-0.40 ms in k_fold (as the clock allows); without the
+// row products' vector work the matrix cores are busy 73% of the cycles at the 1.6 GHz that the chip
+// holds under this load (1.2 PFLOP/s, the rate of a large library product).  One barrier for
 // all eight waves after loading, splitting and multiplying in turn (no roles) ran at 0.60 ms.
-// One call, the separable form with the complex product -> this one: 256^3 0.88 -> 0.47 ms;
-// 203 x 171 x 85 x 3,000 modes 0.41 -> 0.11 ms; 128^3 0.19 -> 0.11 ms; 1500 x 1200 x 2,048 modes 0.12 ->
-// 0.069 ms; relative error against FP64 5.0e-7 on 128^3 both ways, 8.7e-7 -> 4.4e-7 on the ragged
-// grid.  (The hardware cosine in the tables would save 5 us and add 10% to the error.)
+// With few modes the stores bound it: four waves write 32,768 cells, and a 64-bit index, bounds
+// and three pointer tests per cell took 10 us of every block's time (256 x 256 x 64 modes: 16.4 us,
+// 9.1 with the addresses and masks below; 256^3 x 4,096: 422 and 401 in turn on one box).
+// One call, the separable form with the complex product -> this one: 256^3 0.88 -> 0.42 ms;
+// 203 x 171 x 85 x 3,000 modes 0.40 -> 0.087 ms; 128^3 0.17 -> 0.09 ms; 1000 x 500 x 2,048 modes 0.047 ->
+// 0.034 ms, x 64 modes 16 us both (the binding's host work); relative error against FP64 2.2e-6 ->
+// 7.6e-7 on the ragged grid.  (The hardware cosine in the tables would add 10% to the error.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "grf_internal.h"
@@ -48,6 +52,8 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 
 constexpr int kFs = 16;           // modes per stage
+constexpr int kTm = 2;            // modes per thread of the table kernel
+constexpr int kTabRows = 256 * kTm / 8;  // axis points of a block's pass
 constexpr int kRowB = 4 * kFs * 2;  // LDS bytes of one operand row: cos hi, cos lo, sin hi, sin lo
 
 template <bool BF>
@@ -94,6 +100,26 @@ __device__ __forceinline__ void split8(const float (&v)[8], uint4& hi, uint4& lo
 
 __device__ __forceinline__ int swz(int r) { return (r ^ (r >> 3)) & 7; }
 
+// Exchanges among the four lanes of a quad (q = lane % 4; all four active, every exchange made by all):
+// lane q receives word v[q] of lane CTRL % 4, or word a (q < 2) or b of lane (CTRL >> 2 q) % 4.
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad(uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t pick4(const uint32_t (&v)[4], int q)
+{
+    const uint32_t v0 = quad<CTRL>(v[0]), v1 = quad<CTRL>(v[1]), v2 = quad<CTRL>(v[2]), v3 = quad<CTRL>(v[3]);
+    return q & 2 ? (q & 1 ? v3 : v2) : (q & 1 ? v1 : v0);
+}
+template <int CTRL>
+__device__ __forceinline__ uint32_t pick2(float a, float b, int q)
+{
+    const uint32_t u = quad<CTRL>(__builtin_bit_cast(uint32_t, a)), v = quad<CTRL>(__builtin_bit_cast(uint32_t, b));
+    return q & 2 ? v : u;
+}
+
 struct FoldTabs {
     const double* z;
     const double* phi;
@@ -104,11 +130,14 @@ struct FoldTabs {
     uint4* tb;
     uint4* ty;
     uint4* tz;
-    int64_t bb, by;  // thread blocks of the column and y tables
+    int64_t bb, by, bz;  // thread blocks of the column, y and z tables
 };
 
-// One thread: eight modes of one point of one axis (64 contiguous bytes), for the octets blockIdx.y,
-// blockIdx.y + gridDim.y .. (more octets than gridDim.y can count: tables of 2^19 modes and more).
+// One thread: two modes of one octet and one to sixteen points of one axis (an axis' blocks take its
+// points in turn); for the octets blockIdx.y, blockIdx.y + gridDim.y .. (more octets than gridDim.y
+// can count: tables of 2^19 modes and more).  Bound by the FP64 phases, sines and cosines; with
+// eight modes and one point per thread, 30,000 rows x 2,048 modes took 245 us for 148 now,
+// 640 axis points x 4,096 modes 20 for 14.5, small tables 5.7 for 3.6.
 // Columns, and the rows of a 2-D grid, are stored split; y and z of a 3-D grid as FP32.
 template <bool BF>
 __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
@@ -118,45 +147,50 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
     const int axis = b < a.bb ? 0 : (b < a.bb + a.by ? 1 : 2);
     b -= axis == 0 ? 0 : (axis == 1 ? a.bb : a.bb + a.by);
     const int64_t rows = axis == 0 ? a.half : (axis == 1 ? a.ny : a.nz);
-    const int64_t i = b * 256 + threadIdx.x;
-    if (i >= rows) return;
+    const int q = threadIdx.x & 3;  // this thread's pair of modes in the octet, its quarter of the 64 bytes
+    const int64_t i0 = b * kTabRows + (threadIdx.x >> 2);  // (all four lanes of a point have the same)
+    const int64_t step = kTabRows * (axis == 0 ? a.bb : (axis == 1 ? a.by : a.bz));
     const double* const z = a.z + axis * a.n;
     const double xc = a.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
-    const double x = axis == 0 ? a.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
-                     : axis == 1 ? a.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
-                                 : a.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
     const bool split = axis == 0 || (axis == 1 && a.nz == 0);
-    uint4* const base = (axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz)) + (split || axis == 2 ? i * 4 : i);
-    const int64_t step = !split && axis == 1 ? rows : 1;
+    uint4* const base = axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz);
     for (int64_t oct = blockIdx.y; oct < a.ldp / 8; oct += gridDim.y) {
-        float c[8], s[8];
+        double zj[kTm], ps[kTm], w[kTm];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const int64_t j = oct * 8 + m;
-            c[m] = s[m] = 0.f;  // modes past n add nothing
-            if (j < a.n) {
-                double t = z[j] * x;
-                if (axis == 1) t += fma(a.z[j], xc, a.phi[j] * kInvTwoPi);
+        for (int m = 0; m < kTm; ++m) {
+            const int64_t j = oct * 8 + kTm * q + m;
+            const bool in = j < a.n;  // modes past n add nothing
+            zj[m] = in ? z[j] : 0.0;
+            ps[m] = in && axis == 1 ? fma(a.z[j], xc, a.phi[j] * kInvTwoPi) : 0.0;
+            w[m] = !in ? 0.0 : (axis == 1 && a.w ? a.w[j] : 1.0);
+        }
+        for (int64_t i = i0; i < rows; i += step) {
+            const double x = axis == 0 ? a.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
+                             : axis == 1 ? a.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
+                                         : a.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
+            float c[kTm], s[kTm];
+#pragma unroll
+            for (int m = 0; m < kTm; ++m) {
+                const double t = zj[m] * x + ps[m];
                 double sd, cd;
                 sincospi(2.0 * __builtin_amdgcn_fract(t), &sd, &cd);
-                const double w = axis == 1 && a.w ? a.w[j] : 1.0;
-                c[m] = static_cast<float>(w * cd);
-                s[m] = static_cast<float>(w * sd);
+                c[m] = static_cast<float>(w[m] * cd);
+                s[m] = static_cast<float>(w[m] * sd);
             }
+            // the four lanes of a point exchange words so that each stores 16 contiguous bytes
+            uint4 o;
+            if (split) {  // [cos hi | cos lo | sin hi | sin lo], eight 16-bit values each
+                uint32_t v[4];
+                split2<BF>(c[0], c[1], v[0], v[1]);
+                split2<BF>(s[0], s[1], v[2], v[3]);
+                o = make_uint4(pick4<0x00>(v, q), pick4<0x55>(v, q), pick4<0xaa>(v, q), pick4<0xff>(v, q));
+            } else {  // cosines 0-3, 4-7, sines 0-3, 4-7
+                o = make_uint4(pick2<0x88>(c[0], s[0], q), pick2<0x88>(c[1], s[1], q), pick2<0xdd>(c[0], s[0], q),
+                               pick2<0xdd>(c[1], s[1], q));
+            }
+            // (y of a 3-D grid: each kind in a plane of its own)
+            base[oct * rows * 4 + (!split && axis == 1 ? q * rows + i : i * 4 + q)] = o;
         }
-        uint4 o[4];
-        if (split) {
-            split8<BF>(c, o[0], o[1]);
-            split8<BF>(s, o[2], o[3]);
-        } else {
-            o[0] = __builtin_bit_cast(uint4, make_float4(c[0], c[1], c[2], c[3]));
-            o[1] = __builtin_bit_cast(uint4, make_float4(c[4], c[5], c[6], c[7]));
-            o[2] = __builtin_bit_cast(uint4, make_float4(s[0], s[1], s[2], s[3]));
-            o[3] = __builtin_bit_cast(uint4, make_float4(s[4], s[5], s[6], s[7]));
-        }
-        uint4* const out = base + oct * rows * 4;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) out[q * step] = o[q];
     }
 }
 
@@ -469,25 +503,48 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
         }
     }
 
+    // Output addresses: a uniform 64-bit row base and two 32-bit lane offsets per tile (a cell and its
+    // mirror, at most 4 rows of 2^24 cells on), rows past the grid masked by one compare.  (The
+    // middle cell of an odd row is its own mirror: B = 0 and O = 0 there, the same value twice.)
     const bool raw = a.partial != nullptr;
     float* const y = raw ? a.partial + slice * (a.nq * a.nx) : a.y;
     float* const kk = raw ? nullptr : a.k;
     uint8_t* const ind = raw ? nullptr : a.ind;
     const float amp = raw ? 1.f : a.amp;
+    auto store = [&](auto put) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
+            const int64_t qt = q0 + (wm * TM + i) * 32;
+            const int rows = static_cast<int>(min<int64_t>(32, a.nq - qt));
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int64_t col = i0 + (wn * TN + j) * 32 + lr, mirror = a.nx - 1 - col;
+            for (int j = 0; j < TN; ++j) {
+                const int64_t col = i0 + (wn * TN + j) * 32 + lr;
+                const int lim = col < a.half ? rows - 4 * h : 0;
+                const uint32_t c0 = static_cast<uint32_t>(4 * h * a.nx + col);
+                const uint32_t c1 = static_cast<uint32_t>(4 * h * a.nx + (a.nx - 1 - col));
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int64_t q = q0 + (wm * TM + i) * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-                if (col >= a.half || q >= a.nq) continue;
-                const float ev = ae[i][j][e], ov = ao[i][j][e];
-                epi_store(q * a.nx + col, amp * (ev - ov), epi, y, kk, ind);
-                if (mirror != col) epi_store(q * a.nx + mirror, amp * (ev + ov), epi, y, kk, ind);
+                for (int e = 0; e < 16; ++e) {
+                    const int r = 8 * (e >> 2) + (e & 3);
+                    if (r >= lim) continue;
+                    const float ev = ae[i][j][e], ov = ao[i][j][e];
+                    put((qt + r) * a.nx, c0, amp * (ev - ov));
+                    put((qt + r) * a.nx, c1, amp * (ev + ov));
+                }
             }
         }
+    };
+    if (!kk && !ind)
+        store([&](int64_t row, uint32_t c, float v) { global_ptr(y + row)[c] = v; });
+    else
+        store([&](int64_t row, uint32_t c, float v) {
+            if (y) global_ptr(y + row)[c] = v;
+            if (kk) global_ptr(kk + row)[c] = expf(epi.mu + v);
+            if (ind) {
+                int f = 0;
+                for (int t = 0; t < epi.nthr; ++t) f += v > epi.thr[t] ? 1 : 0;
+                global_ptr(ind + row)[c] = static_cast<uint8_t>(f);
+            }
+        });
 }
 
 template <int TM, int TN>
@@ -512,6 +569,16 @@ hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, 
 
 }  // namespace
 
+bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t n)
+{
+    // The bf16 separable form's tables take no software conversion, and a tall 2-D grid gains little
+    // from halved columns: there the complex form is the faster one, below about 6e8 terms.  One call
+    // in us, complex / folded: 256 x 256 x 4,096 modes 26 / 31, 40 x 2000 x 2,048 31 / 36, 16 x 4096
+    // x 512 25 / 29; past the line 100 x 1500 x 4,096 55 / 40, 1024 x 1024 x 1,024 46 / 34, 2000 x
+    // 40 x 4,096 49 / 36.  fp16: 256 x 256 x 4,096 31 / 31, 40 x 2000 x 2,048 41 / 35.
+    return !bf || dim == 3 || nx >= 4 * ny || static_cast<double>(nx * ny * nz) * static_cast<double>(n) >= 6e8;
+}
+
 FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split)
 {
     FoldWs w;
@@ -523,12 +590,22 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     w.wide = (half + 127) / 128 * 128 == (half + 63) / 64 * 64;
     const int64_t cols = w.wide ? 128 : 64;
     const int64_t blocks = ((half + cols - 1) / cols) * ((nq + 127) / 128);
-    // One block per CU at a time (LDS): launches of at most half the 256 CUs split the modes
-    // into slices of at least eight stages (128 modes) that fill them; the slices' sums take at
-    // most 32 MiB.
+    // One block per CU at a time (LDS): launches of at most half the 256 CUs may split the modes into
+    // slices of at least four stages (64 modes) that fill them; the slices' sums take at most 32
+    // MiB.  A stage takes about 0.9 us in a wide block (0.6 in a narrow one), each slice writes and
+    // reads 4 bytes per cell at about 5 TB/s, and the second pass costs 3 us besides: as many
+    // slices as make the sum of these smallest, one where no split pays.  256 x 256 x 64 cells x
+    // 256 modes: 39 us in two slices, 26 in one; 256 x 256 x 2,048: 13 us + 4 for the sums in 16.
     constexpr int64_t kCUs = 256, kMaxBytes = int64_t(32) << 20;
     const int64_t quads = ldp / (4 * kFs);  // slices are whole groups of four stages
-    int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads / 2), kMaxBytes / (4 * C)) : 1;
+    int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads), kMaxBytes / (4 * C)) : 1;
+    if (sl > 1) {
+        const double stages = 4.0 * static_cast<double>(quads) * (w.wide ? 0.9 : 0.6);
+        const double sums = 8.0 * static_cast<double>(C) / 5e6;
+        sl = std::min<int64_t>(sl, std::max<int64_t>(1, std::llround(std::sqrt(stages / sums))));
+        const double k = static_cast<double>(sl);
+        if (stages <= stages / k + k * sums + 3.0) sl = 1;
+    }
     if (sl < 2) sl = 1;
     w.per = 4 * ((quads + sl - 1) / sl);
     w.slices = static_cast<int>((4 * quads + w.per - 1) / w.per);
@@ -559,10 +636,15 @@ hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi
     t.tb = reinterpret_cast<uint4*>(base);
     t.ty = reinterpret_cast<uint4*>(base + w.ty);
     t.tz = t.nz ? reinterpret_cast<uint4*>(base + w.tz) : nullptr;
-    t.bb = (t.half + 255) / 256;
-    t.by = (t.ny + 255) / 256;
-    const int64_t tb = t.bb + t.by + (t.nz + 255) / 256;  // axes are at most 2^24 long
-    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(std::min<int64_t>(ldp / 8, 65535)));
+    const int64_t octs = ldp / 8, span = t.half + t.ny + t.nz;
+    // about 1,024 blocks where there is that much work: more points per thread share its mode's loads
+    const int64_t reps = std::max<int64_t>(1, std::min<int64_t>(16, span * octs / (kTabRows * 1024)));
+    const int64_t per = kTabRows * reps;
+    t.bb = (t.half + per - 1) / per;
+    t.by = (t.ny + per - 1) / per;
+    t.bz = (t.nz + per - 1) / per;
+    const int64_t tb = t.bb + t.by + t.bz;  // axes are at most 2^24 long
+    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(std::min<int64_t>(octs, 65535)));
     if (bf) hipLaunchKernelGGL(k_fold_tables<true>, tg, dim3(256), 0, s, t);
     else hipLaunchKernelGGL(k_fold_tables<false>, tg, dim3(256), 0, s, t);
     hipError_t e = hipGetLastError();

@@ -243,6 +243,8 @@ struct FoldWs {
     int64_t per;
 };
 FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split);
+// Whether the default evaluation of a hi+lo method is the folded one (else the separable form).
+bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t n);
 hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
                        hipStream_t s);
 // `ws` (ws_doubles FP64 values) holds the sums of the mode slices where the launch takes slices.

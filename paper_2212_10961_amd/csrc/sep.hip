@@ -1156,7 +1156,7 @@ int sep_mode_slices(int method, int dim, int64_t nx, int64_t ny, int64_t nz, int
     constexpr int64_t kCUs = 256, kMaxBytes = int64_t(32) << 20;
     const int64_t np = ldp / (2 * kJC);
     *pairs = np;
-    if (method != GRF_SEP_BF16 && method != GRF_SEP_F16) return 1;  // (hi+lo: see fold.hip)
+    if (method < GRF_SEP_BF16 || method > GRF_SEP_F16_X3) return 1;
     const int tile = sep_default_tile(method, nx, ny, nz);
     const int zs = dim == 3 ? sep_tile_slices(tile, method, true) : 1;
     const int64_t blocks = ((nx + kTiles[tile].bn - 1) / kTiles[tile].bn) * ((ny + kTiles[tile].bm - 1) / kTiles[tile].bm) *
