@@ -407,7 +407,7 @@ static int grid_launch(const grf_modes* modes, const grf_grid* grid, int method,
 {
     if (tile < 0 && folds(modes, grid, method)) {
         GRF_HIP(launch_fold(direct_grid_args(modes, grid, y, k, ind), padded_modes(modes->n), is_bf16(method), e, ws,
-                            allow_split, true, s));
+                            allow_split, s));
         return GRF_OK;
     }
     GridWs w = grid_ws(modes, grid, method, ws);
@@ -565,9 +565,20 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
     GRF_HIP(aligned_modes(m1, k1, s, &a1));
     GRF_HIP(aligned_modes(m2, k2, s, &a2));
     GRF_HIP(launch_rule_tables(*rule, rt, s));
-    // (hi+lo tables of different padded lengths run one after the other)
-    if (is_sep(method) && !folds(&a1, grid, method) && !folds(&a2, grid, method) &&
-        (!is_hilo(method) || padded_modes(a1.n) == padded_modes(a2.n))) {
+    const int64_t ldp = padded_modes(a1.n);
+    if (folds(&a1, grid, method) && folds(&a2, grid, method) && padded_modes(a2.n) == ldp) {
+        FoldPair p;
+        const DirectGrid d1 = direct_grid_args(&a1, grid, f1, nullptr, nullptr);
+        const DirectGrid d2 = direct_grid_args(&a2, grid, f2, nullptr, nullptr);
+        GRF_HIP(launch_fold_pair(d1, d2, ldp, is_bf16(method), tabs,
+                                 static_cast<char*>(tabs) + grid_ws(&a1, grid, method, nullptr).bytes, &p, s));
+        if (p.slices > 1) {
+            GRF_HIP(launch_pluri_slices(p.p1, p.p2, p.slices, C, d1.amp, d2.amp, make_pluri(rule, rt), facies, value,
+                                        y1, y2, s));
+            return GRF_OK;
+        }
+    } else if (is_sep(method) && !folds(&a1, grid, method) && !folds(&a2, grid, method) &&
+               (!is_hilo(method) || padded_modes(a2.n) == ldp)) {  // (other hi+lo pairs run one after the other)
         // both fields: one launch of the six (2-D: four) tables, one of the contraction
         const GridWs w1 = grid_ws(&a1, grid, method, tabs);
         const GridWs w2 = grid_ws(&a2, grid, method, static_cast<char*>(tabs) + w1.bytes);

@@ -120,16 +120,23 @@ __device__ __forceinline__ uint32_t pick2(float a, float b, int q)
     return q & 2 ? v : u;
 }
 
-struct FoldTabs {
+// One field's mode table and where its axis tables go.
+struct FoldField {
     const double* z;
     const double* phi;
     const double* w;
-    double fs[3], o[3], h[3];
-    int64_t n, ldp, half, ny, nz;  // nz = 0: no z table
-    double nx;
+    double fs[3];
+    int64_t n;
     uint4* tb;
     uint4* ty;
     uint4* tz;
+};
+
+struct FoldTabs {
+    FoldField f0, f1;  // f1: the second field of a pair (blockIdx.z = 1)
+    double o[3], h[3];
+    int64_t ldp, half, ny, nz;  // nz = 0: no z table
+    double nx;
     int64_t bb, by, bz;  // thread blocks of the column, y and z tables
 };
 
@@ -143,6 +150,7 @@ template <bool BF>
 __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
 {
     constexpr double kInvTwoPi = 0.15915494309189533576888376337251;
+    const FoldField f = blockIdx.z ? a.f1 : a.f0;
     int64_t b = blockIdx.x;
     const int axis = b < a.bb ? 0 : (b < a.bb + a.by ? 1 : 2);
     b -= axis == 0 ? 0 : (axis == 1 ? a.bb : a.bb + a.by);
@@ -150,24 +158,24 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
     const int q = threadIdx.x & 3;  // this thread's pair of modes in the octet, its quarter of the 64 bytes
     const int64_t i0 = b * kTabRows + (threadIdx.x >> 2);  // (all four lanes of a point have the same)
     const int64_t step = kTabRows * (axis == 0 ? a.bb : (axis == 1 ? a.by : a.bz));
-    const double* const z = a.z + axis * a.n;
-    const double xc = a.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
+    const double* const z = f.z + axis * f.n;
+    const double xc = f.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
     const bool split = axis == 0 || (axis == 1 && a.nz == 0);
-    uint4* const base = axis == 0 ? a.tb : (axis == 1 ? a.ty : a.tz);
+    uint4* const base = axis == 0 ? f.tb : (axis == 1 ? f.ty : f.tz);
     for (int64_t oct = blockIdx.y; oct < a.ldp / 8; oct += gridDim.y) {
         double zj[kTm], ps[kTm], w[kTm];
 #pragma unroll
         for (int m = 0; m < kTm; ++m) {
             const int64_t j = oct * 8 + kTm * q + m;
-            const bool in = j < a.n;  // modes past n add nothing
+            const bool in = j < f.n;  // modes past n add nothing
             zj[m] = in ? z[j] : 0.0;
-            ps[m] = in && axis == 1 ? fma(a.z[j], xc, a.phi[j] * kInvTwoPi) : 0.0;
-            w[m] = !in ? 0.0 : (axis == 1 && a.w ? a.w[j] : 1.0);
+            ps[m] = in && axis == 1 ? fma(f.z[j], xc, f.phi[j] * kInvTwoPi) : 0.0;
+            w[m] = !in ? 0.0 : (axis == 1 && f.w ? f.w[j] : 1.0);
         }
         for (int64_t i = i0; i < rows; i += step) {
-            const double x = axis == 0 ? a.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
-                             : axis == 1 ? a.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
-                                         : a.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
+            const double x = axis == 0 ? f.fs[0] * ((static_cast<double>(i) + 0.5 - 0.5 * a.nx) * a.h[0])
+                             : axis == 1 ? f.fs[1] * (a.o[1] + (static_cast<double>(i) + 0.5) * a.h[1])
+                                         : f.fs[2] * (a.o[2] + (static_cast<double>(i) + 0.5) * a.h[2]);
             float c[kTm], s[kTm];
 #pragma unroll
             for (int m = 0; m < kTm; ++m) {
@@ -194,18 +202,24 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
     }
 }
 
-struct FoldArgs {
+// One field's axis tables and outputs.
+struct FoldSum {
     const uint4* tb;
     const uint4* ty;
     const uint4* tz;
-    int64_t nx, half, ny, nz, nq;
-    int64_t stages, per;  // 16-mode stages in all and per slice, multiples of 4
-    int64_t tiles_i, tiles, items;  // column tiles; tiles of one slice; tiles of all slices
     float amp;
     float* y;
+    float* partial;  // raw sums [slice][nq nx] of a launch whose modes are split, or nullptr
+};
+
+struct FoldArgs {
+    FoldSum f0, f1;  // f1: the second field of a pair (the second half of the items)
+    int64_t nx, half, ny, nz, nq;
+    int64_t stages, per;  // 16-mode stages in all and per slice, multiples of 4
+    int64_t tiles_i, tiles;      // column tiles; tiles of one slice
+    int64_t field_items, items;  // tiles of all slices of one field, of all fields
     float* k;
     uint8_t* ind;
-    float* partial;  // raw sums [slice][nq nx] of a launch whose modes are split, or nullptr
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -261,8 +275,11 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
     // consecutive work items (slice by slice, columns fastest), whose blocks read the same table
     // stages at the same time.  (gridDim.x is a multiple of 8.)
     const int64_t bid = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-    const int64_t item = (bid & 7) * (static_cast<int64_t>(gridDim.y) * (gridDim.x >> 3)) + (bid >> 3);
+    int64_t item = (bid & 7) * (static_cast<int64_t>(gridDim.y) * (gridDim.x >> 3)) + (bid >> 3);
     if (item >= a.items) return;  // the whole block
+    const bool second = item >= a.field_items;
+    const FoldSum f = second ? a.f1 : a.f0;
+    item -= second ? a.field_items : 0;
     const int64_t slice = item / a.tiles, tile = item - slice * a.tiles;
     const int64_t i0 = tile % a.tiles_i * BN, q0 = tile / a.tiles_i * BM;
     const int64_t s0 = slice * a.per, s1 = min(a.stages, s0 + a.per);
@@ -289,9 +306,9 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
             offb[k] = source(rb, i0, a.half);
             ldb[k] = rb * 8 * kRowB;
         }
-        const char* gb = reinterpret_cast<const char*>(a.tb) + 2 * s0 * a.half * 64;
-        const char* ga = reinterpret_cast<const char*>(a.ty) + 2 * s0 * a.ny * 64;
-        const char* gz = D3 ? reinterpret_cast<const char*>(a.tz) + 2 * s0 * a.nz * 64 : nullptr;
+        const char* gb = reinterpret_cast<const char*>(f.tb) + 2 * s0 * a.half * 64;
+        const char* ga = reinterpret_cast<const char*>(f.ty) + 2 * s0 * a.ny * 64;
+        const char* gz = D3 ? reinterpret_cast<const char*>(f.tz) + 2 * s0 * a.nz * 64 : nullptr;
         const int64_t stepb = 128 * a.half, stepa = 128 * a.ny, stepz = 128 * a.nz;
         // 3-D: this wave makes octet pw % 2 of the rows 64 (pw / 2) + l
         const int row = (pw >> 1) * 64 + l, oct = pw & 1;
@@ -456,24 +473,24 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
             const int r = (wn * TN + j) * 32 + lr;
             fb[j][kind] = r * kRowB + (((4 * h + kind) ^ swz(r)) << 4);
         }
-    auto read = [&](int buf, int half, Frag& f) {
+    auto read = [&](int buf, int half, Frag& g) {
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-                f.a[i][x] = *reinterpret_cast<const uint4*>(sa + buf * kA + fa[i][2 * half + x]);
+                g.a[i][x] = *reinterpret_cast<const uint4*>(sa + buf * kA + fa[i][2 * half + x]);
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                f.b[j][x] = *reinterpret_cast<const uint4*>(sb + buf * kB + fb[j][2 * half + x]);
+                g.b[j][x] = *reinterpret_cast<const uint4*>(sb + buf * kB + fb[j][2 * half + x]);
         }
     };
-    auto mac = [&](const Frag& f, f32x16(&acc)[TM][TN]) {
+    auto mac = [&](const Frag& g, f32x16(&acc)[TM][TN]) {
 #pragma unroll
         for (int p = 0; p < 3; ++p)  // hi hi, hi lo, lo hi
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = mma<BF>(f.a[i][p == 2], f.b[j][p == 1], acc[i][j]);
+                for (int j = 0; j < TN; ++j) acc[i][j] = mma<BF>(g.a[i][p == 2], g.b[j][p == 1], acc[i][j]);
     };
     // the reads of the next half ride along the products of this one
     auto interleave = [&]() {
@@ -506,11 +523,11 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
     // Output addresses: a uniform 64-bit row base and two 32-bit lane offsets per tile (a cell and its
     // mirror, at most 4 rows of 2^24 cells on), rows past the grid masked by one compare.  (The
     // middle cell of an odd row is its own mirror: B = 0 and O = 0 there, the same value twice.)
-    const bool raw = a.partial != nullptr;
-    float* const y = raw ? a.partial + slice * (a.nq * a.nx) : a.y;
+    const bool raw = f.partial != nullptr;
+    float* const y = raw ? f.partial + slice * (a.nq * a.nx) : f.y;
     float* const kk = raw ? nullptr : a.k;
     uint8_t* const ind = raw ? nullptr : a.ind;
-    const float amp = raw ? 1.f : a.amp;
+    const float amp = raw ? 1.f : f.amp;
     auto store = [&](auto put) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -540,24 +557,25 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
             if (y) global_ptr(y + row)[c] = v;
             if (kk) global_ptr(kk + row)[c] = expf(epi.mu + v);
             if (ind) {
-                int f = 0;
-                for (int t = 0; t < epi.nthr; ++t) f += v > epi.thr[t] ? 1 : 0;
-                global_ptr(ind + row)[c] = static_cast<uint8_t>(f);
+                int facies = 0;
+                for (int t = 0; t < epi.nthr; ++t) facies += v > epi.thr[t] ? 1 : 0;
+                global_ptr(ind + row)[c] = static_cast<uint8_t>(facies);
             }
         });
 }
 
 template <int TM, int TN>
-hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, hipStream_t s)
+hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, int fields, hipStream_t s)
 {
     FoldArgs a = a0;
     a.tiles_i = (a.half + 64 * TN - 1) / (64 * TN);
     a.tiles = a.tiles_i * ((a.nq + 64 * TM - 1) / (64 * TM));
-    a.items = a.tiles * slices;
+    a.field_items = a.tiles * slices;
+    a.items = fields * a.field_items;
     const int64_t gy = (a.items + kMaxGridX - 1) / kMaxGridX;
     if (gy > 65535) return hipErrorInvalidValue;
     const dim3 g(static_cast<unsigned>((((a.items + gy - 1) / gy) + 7) / 8 * 8), static_cast<unsigned>(gy)), b(512);
-    if (a.tz) {
+    if (a.f0.tz) {
         if (bf) hipLaunchKernelGGL((k_fold<TM, TN, true, true>), g, b, 0, s, a, epi);
         else hipLaunchKernelGGL((k_fold<TM, TN, false, true>), g, b, 0, s, a, epi);
     } else {
@@ -579,7 +597,7 @@ bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t 
     return !bf || dim == 3 || nx >= 4 * ny || static_cast<double>(nx * ny * nz) * static_cast<double>(n) >= 6e8;
 }
 
-FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split)
+FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split, int fields)
 {
     FoldWs w;
     const int64_t half = (nx + 1) / 2, nq = ny * nz, C = nq * nx;
@@ -589,7 +607,7 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     // 128 rows x 128 columns per block, 64 columns where that covers fewer
     w.wide = (half + 127) / 128 * 128 == (half + 63) / 64 * 64;
     const int64_t cols = w.wide ? 128 : 64;
-    const int64_t blocks = ((half + cols - 1) / cols) * ((nq + 127) / 128);
+    const int64_t blocks = fields * ((half + cols - 1) / cols) * ((nq + 127) / 128);
     // One block per CU at a time (LDS): launches of at most half the 256 CUs may split the modes into
     // slices of at least four stages (64 modes) that fill them; the slices' sums take at most 32
     // MiB.  A stage takes about 0.9 us in a wide block (0.6 in a narrow one), each slice writes and
@@ -601,7 +619,7 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads), kMaxBytes / (4 * C)) : 1;
     if (sl > 1) {
         const double stages = 4.0 * static_cast<double>(quads) * (w.wide ? 0.9 : 0.6);
-        const double sums = 8.0 * static_cast<double>(C) / 5e6;
+        const double sums = 8.0 * static_cast<double>(fields * C) / 5e6;
         sl = std::min<int64_t>(sl, std::max<int64_t>(1, std::llround(std::sqrt(stages / sums))));
         const double k = static_cast<double>(sl);
         if (stages <= stages / k + k * sums + 3.0) sl = 1;
@@ -613,29 +631,36 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     return w;
 }
 
-hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
-                       hipStream_t s)
+static FoldField fold_field(const DirectGrid& d, const FoldWs& w, void* ws)
 {
-    const FoldWs w = fold_ws(d.nx, d.ny, d.nq / d.ny, ldp, d.dim, split);
     char* const base = static_cast<char*>(ws);
+    return {d.z, d.phi, d.w, {d.fs[0], d.fs[1], d.fs[2]}, d.n, reinterpret_cast<uint4*>(base),
+            reinterpret_cast<uint4*>(base + w.ty), d.dim == 3 ? reinterpret_cast<uint4*>(base + w.tz) : nullptr};
+}
+
+static FoldSum fold_sum(const DirectGrid& d, const FoldWs& w, void* ws)
+{
+    const FoldField f = fold_field(d, w, ws);
+    return {f.tb, f.ty, f.tz, d.amp, d.y,
+            w.slices > 1 ? reinterpret_cast<float*>(static_cast<char*>(ws) + w.partial) : nullptr};
+}
+
+// The tables of one field, or of two on the same grid (d2 not null) by one launch.
+static hipError_t fold_tables(const DirectGrid& d, const DirectGrid* d2, int64_t ldp, bool bf, const FoldWs& w,
+                              void* ws, void* ws2, hipStream_t s)
+{
     FoldTabs t{};
-    t.z = d.z;
-    t.phi = d.phi;
-    t.w = d.w;
+    t.f0 = fold_field(d, w, ws);
+    if (d2) t.f1 = fold_field(*d2, w, ws2);
     for (int a = 0; a < 3; ++a) {
-        t.fs[a] = d.fs[a];
         t.o[a] = d.o[a];
         t.h[a] = d.h[a];
     }
-    t.n = d.n;
     t.ldp = ldp;
     t.half = (static_cast<int64_t>(d.nx) + 1) / 2;
     t.ny = d.ny;
     t.nz = d.dim == 3 ? d.nq / d.ny : 0;
     t.nx = static_cast<double>(d.nx);
-    t.tb = reinterpret_cast<uint4*>(base);
-    t.ty = reinterpret_cast<uint4*>(base + w.ty);
-    t.tz = t.nz ? reinterpret_cast<uint4*>(base + w.tz) : nullptr;
     const int64_t octs = ldp / 8, span = t.half + t.ny + t.nz;
     // about 1,024 blocks where there is that much work: more points per thread share its mode's loads
     const int64_t reps = std::max<int64_t>(1, std::min<int64_t>(16, span * octs / (kTabRows * 1024)));
@@ -644,32 +669,57 @@ hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi
     t.by = (t.ny + per - 1) / per;
     t.bz = (t.nz + per - 1) / per;
     const int64_t tb = t.bb + t.by + t.bz;  // axes are at most 2^24 long
-    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(std::min<int64_t>(octs, 65535)));
+    const dim3 tg(static_cast<unsigned>(tb), static_cast<unsigned>(std::min<int64_t>(octs, 65535)), d2 ? 2 : 1);
     if (bf) hipLaunchKernelGGL(k_fold_tables<true>, tg, dim3(256), 0, s, t);
     else hipLaunchKernelGGL(k_fold_tables<false>, tg, dim3(256), 0, s, t);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    return hipGetLastError();
+}
 
+// Their contraction, likewise.
+static hipError_t fold_sums(const DirectGrid& d, const DirectGrid* d2, int64_t ldp, bool bf, const Epi& epi,
+                            const FoldWs& w, void* ws, void* ws2, hipStream_t s)
+{
     FoldArgs a{};
-    a.tb = t.tb;
-    a.ty = t.ty;
-    a.tz = t.tz;
+    a.f0 = fold_sum(d, w, ws);
+    if (d2) a.f1 = fold_sum(*d2, w, ws2);
     a.nx = d.nx;
-    a.half = t.half;
+    a.half = (static_cast<int64_t>(d.nx) + 1) / 2;
     a.ny = d.ny;
-    a.nz = t.nz;
+    a.nz = d.dim == 3 ? d.nq / d.ny : 0;
     a.nq = d.nq;
     a.stages = ldp / kFs;
     a.per = w.per;
-    a.amp = d.amp;
-    a.y = d.y;
     a.k = d.k;
     a.ind = d.ind;
-    a.partial = w.slices > 1 ? reinterpret_cast<float*>(base + w.partial) : nullptr;
-    TimedScope scope(s, timed);
-    e = w.wide ? launch_tile<2, 2>(a, epi, bf, w.slices, s) : launch_tile<2, 1>(a, epi, bf, w.slices, s);
+    return w.wide ? launch_tile<2, 2>(a, epi, bf, w.slices, d2 ? 2 : 1, s)
+                  : launch_tile<2, 1>(a, epi, bf, w.slices, d2 ? 2 : 1, s);
+}
+
+hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, hipStream_t s)
+{
+    const FoldWs w = fold_ws(d.nx, d.ny, d.nq / d.ny, ldp, d.dim, split, 1);
+    hipError_t e = fold_tables(d, nullptr, ldp, bf, w, ws, nullptr, s);
+    if (e != hipSuccess) return e;
+    TimedScope scope(s);  // the contraction and the slice sums
+    e = fold_sums(d, nullptr, ldp, bf, epi, w, ws, nullptr, s);
     if (e != hipSuccess || w.slices == 1) return e;
-    return launch_points_reduce(a.partial, w.slices, d.nq * d.nx, d.amp, epi, d.y, d.k, d.ind, s);
+    return launch_points_reduce(reinterpret_cast<float*>(static_cast<char*>(ws) + w.partial), w.slices, d.nq * d.nx,
+                                d.amp, epi, d.y, d.k, d.ind, s);
+}
+
+hipError_t launch_fold_pair(const DirectGrid& d1, const DirectGrid& d2, int64_t ldp, bool bf, void* ws1, void* ws2,
+                            FoldPair* out, hipStream_t s)
+{
+    const FoldWs w = fold_ws(d1.nx, d1.ny, d1.nq / d1.ny, ldp, d1.dim, true, 2);
+    *out = {nullptr, nullptr, w.slices};
+    if (w.slices > 1) {
+        out->p1 = reinterpret_cast<float*>(static_cast<char*>(ws1) + w.partial);
+        out->p2 = reinterpret_cast<float*>(static_cast<char*>(ws2) + w.partial);
+    }
+    const hipError_t e = fold_tables(d1, &d2, ldp, bf, w, ws1, ws2, s);
+    if (e != hipSuccess) return e;
+    TimedScope scope(s);
+    return fold_sums(d1, &d2, ldp, bf, Epi{}, w, ws1, ws2, s);
 }
 
 }  // namespace grf

@@ -234,7 +234,8 @@ hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream
 
 // ---------------------------------------------------------------- folded split-precision grid sum (fold.hip)
 // Offsets of its tables (columns at 0) and slice sums in the workspace, and its launch plan;
-// `split` = false plans without the slices.
+// `split` = false plans without the slices; `fields` = 2 plans a pair in one launch, whose slice sums
+// are never more than one field's own.
 struct FoldWs {
     size_t ty, tz, partial;
     size_t split_bytes;  // of the slice sums
@@ -242,11 +243,20 @@ struct FoldWs {
     int slices;          // mode slices (1: no split) of `per` stages each
     int64_t per;
 };
-FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split);
+FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split, int fields = 1);
 // Whether the default evaluation of a hi+lo method is the folded one (else the separable form).
 bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t n);
-hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, bool timed,
-                       hipStream_t s);
+hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, hipStream_t s);
+// Two fields on one grid (tables of one padded length) by one launch of the tables and one of the
+// contraction, each with a workspace of fold_ws; out: the slice sums where the modes are split
+// (slices > 1; the fields are not stored then).
+struct FoldPair {
+    float* p1;
+    float* p2;
+    int slices;
+};
+hipError_t launch_fold_pair(const DirectGrid& d1, const DirectGrid& d2, int64_t ldp, bool bf, void* ws1, void* ws2,
+                            FoldPair* out, hipStream_t s);
 // `ws` (ws_doubles FP64 values) holds the sums of the mode slices where the launch takes slices.
 hipError_t launch_direct_grid_f64(const DirectGrid& g, const Epi& epi, double* ws, size_t ws_doubles, hipStream_t s);
 // `partial` (workspace, points_mode_slices(P, n) * P floats when that is > 1) receives the
