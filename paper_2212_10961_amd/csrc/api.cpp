@@ -176,10 +176,19 @@ static int resolve_grid_method(int method, const grf_grid* g)
     return method;
 }
 
+int fold_axis(const grf_grid* g, int dim)
+{
+    int a = 0;
+    while (a < dim - 1 && g->n[a] == 1) ++a;
+    return a;
+}
+
 // Whether a method's default evaluation on this grid is the folded contraction (fold.hip).
 static bool folds(const grf_modes* m, const grf_grid* g, int method)
 {
-    return is_hilo(method) && fold_default(is_bf16(method), m->dim, g->n[0], g->n[1], g->n[2], m->n);
+    const int a = fold_axis(g, m->dim), b = (a + 1) % m->dim;
+    return is_hilo(method) && fold_default(is_bf16(method), m->dim, g->n[a], g->n[b],
+                                           m->dim == 3 ? g->n[(a + 2) % 3] : 1, m->n);
 }
 
 GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
@@ -217,7 +226,8 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
     // the folded evaluation keeps its tables, never larger than the ones above (which explicit tiles
     // take), and its slice sums here instead
     if (fold) {
-        const FoldWs f = fold_ws(g->n[0], g->n[1], g->n[2], ldp, dim, true);
+        const int a = fold_axis(g, dim);
+        const FoldWs f = fold_ws(g->n[a], g->n[(a + 1) % dim], dim == 3 ? g->n[(a + 2) % 3] : 1, ldp, dim, true);
         const size_t tables = c.used;
         c.used = std::max(c.used, f.partial + f.split_bytes);
         w.split_bytes = c.used - tables;
@@ -294,18 +304,26 @@ int grid_table_descs(const grf_modes* m, const grf_grid* g, int method, const Gr
 DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind)
 {
     DirectGrid d{};
-    d.z = m->z;
+    const int first = fold_axis(g, m->dim);
+    const double* z[3] = {nullptr, nullptr, nullptr};
+    int64_t n[3] = {1, 1, 1};
+    for (int a = 0; a < m->dim; ++a) {
+        const int c = (first + a) % m->dim;
+        z[a] = m->z + c * m->n;
+        n[a] = g->n[c];
+        d.fs[a] = 1.0 / (6.283185307179586476925286766559 * m->ell[c]);
+        d.o[a] = g->origin[c];
+        d.h[a] = g->h[c];
+    }
+    d.zx = z[0];
+    d.zy = z[1];
+    d.zz = z[2];
     d.phi = m->phi;
     d.w = m->w;
-    for (int a = 0; a < 3; ++a) {
-        d.fs[a] = a < m->dim ? 1.0 / (6.283185307179586476925286766559 * m->ell[a]) : 0.0;
-        d.o[a] = a < m->dim ? g->origin[a] : 0.0;
-        d.h[a] = a < m->dim ? g->h[a] : 0.0;
-    }
-    d.ny = g->n[1];
-    d.nq = g->n[1] * g->n[2];
+    d.ny = n[1];
+    d.nq = n[1] * n[2];
     d.n = m->n;
-    d.nx = static_cast<int32_t>(g->n[0]);
+    d.nx = static_cast<int32_t>(n[0]);
     d.dim = m->dim;
     d.amp64 = m->sigma * std::sqrt(2.0 / static_cast<double>(m->n));
     d.amp = static_cast<float>(d.amp64);

@@ -351,7 +351,7 @@ static int build_plan(grf_plan* p, const grf_batch_item* items, int32_t n, hipSt
             DirectBatchItem& d = di[r];
             d.g = direct_grid_args(&it.modes, &it.grid, it.y, it.k, it.ind);
             d.epi = make_epi(&it.epi);
-            d.tiles_i = (it.grid.n[0] + kDirectTile - 1) / kDirectTile;
+            d.tiles_i = (d.g.nx + kDirectTile - 1) / kDirectTile;
             d.item0 = item;
             item += d.tiles_i * ((d.g.nq + kDirectTile - 1) / kDirectTile);
         }

@@ -178,14 +178,15 @@ __device__ __forceinline__ void direct_tile(const DirectGrid& g, const Epi& epi,
     const int64_t j0 = min(n0 + w * mc, n1), j1 = min(j0 + mc, n1);
     double4* const sm = reinterpret_cast<double4*>(smem) + w * kDgStage;
     R* const sw = reinterpret_cast<R*>(smem + kDgWaves * kDgStage * 32) + w * kDgStage;
-    const double* const zy = g.z + n;
-    const double* const z3 = g.dim == 3 ? g.z + 2 * n : nullptr;
+    const double* const zx = g.zx;
+    const double* const zy = g.zy;
+    const double* const z3 = g.zz;
 
     // modes past the chunk's end stage the table's last entry of the chunk; their row operands
     // are set to zero below
     auto fetch = [&](int64_t j) {
         const int64_t jj = min(j + l, j1 - 1);
-        return make_double4(g.z[jj], zy[jj], z3 ? z3[jj] : 0.0, g.phi[jj] * kInvTwoPi);
+        return make_double4(zx[jj], zy[jj], z3 ? z3[jj] : 0.0, g.phi[jj] * kInvTwoPi);
     };
     auto fetch_w = [&](int64_t j) { return WT ? static_cast<R>(g.w[min(j + l, j1 - 1)]) : R(1); };
     double4 nm = make_double4(0.0, 0.0, 0.0, 0.0);
@@ -573,7 +574,10 @@ hipError_t launch_direct_grid_f64(const DirectGrid& g0, const Epi& epi, double* 
     g.partial64 = nullptr;
     const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2, C = g.nq * g.nx;
     // an operand costs several matrix steps: four row tiles per column operand once they fill the CUs
-    if (((half + 15) / 16) * ((g.nq + 63) / 64) >= 256) return launch_direct_tile<double, 16, 4>(g, epi, s);
+    // (five operands for 64 rows; one row tile takes two for 16, fewer up to 32 rows: 65,536 x 1 cells
+    // x 1,000 modes 121 us for 340)
+    if (g.nq > 32 && ((half + 15) / 16) * ((g.nq + 63) / 64) >= 256)
+        return launch_direct_tile<double, 16, 4>(g, epi, s);
     // few tiles: slices of at least 128 modes spread the operands over more CUs (a second launch
     // adds the slices in order), where the workspace holds their sums
     const int64_t tiles = ((half + 15) / 16) * ((g.nq + 15) / 16);

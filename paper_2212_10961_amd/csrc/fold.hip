@@ -122,7 +122,9 @@ __device__ __forceinline__ uint32_t pick2(float a, float b, int q)
 
 // One field's mode table and where its axis tables go.
 struct FoldField {
-    const double* z;
+    const double* zx;
+    const double* zy;
+    const double* zz;
     const double* phi;
     const double* w;
     double fs[3];
@@ -158,7 +160,7 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
     const int q = threadIdx.x & 3;  // this thread's pair of modes in the octet, its quarter of the 64 bytes
     const int64_t i0 = b * kTabRows + (threadIdx.x >> 2);  // (all four lanes of a point have the same)
     const int64_t step = kTabRows * (axis == 0 ? a.bb : (axis == 1 ? a.by : a.bz));
-    const double* const z = f.z + axis * f.n;
+    const double* const z = axis == 0 ? f.zx : (axis == 1 ? f.zy : f.zz);
     const double xc = f.fs[0] * (a.o[0] + 0.5 * a.nx * a.h[0]);
     const bool split = axis == 0 || (axis == 1 && a.nz == 0);
     uint4* const base = axis == 0 ? f.tb : (axis == 1 ? f.ty : f.tz);
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(256) void k_fold_tables(FoldTabs a)
             const int64_t j = oct * 8 + kTm * q + m;
             const bool in = j < f.n;  // modes past n add nothing
             zj[m] = in ? z[j] : 0.0;
-            ps[m] = in && axis == 1 ? fma(f.z[j], xc, f.phi[j] * kInvTwoPi) : 0.0;
+            ps[m] = in && axis == 1 ? fma(f.zx[j], xc, f.phi[j] * kInvTwoPi) : 0.0;
             w[m] = !in ? 0.0 : (axis == 1 && f.w ? f.w[j] : 1.0);
         }
         for (int64_t i = i0; i < rows; i += step) {
@@ -634,7 +636,7 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
 static FoldField fold_field(const DirectGrid& d, const FoldWs& w, void* ws)
 {
     char* const base = static_cast<char*>(ws);
-    return {d.z, d.phi, d.w, {d.fs[0], d.fs[1], d.fs[2]}, d.n, reinterpret_cast<uint4*>(base),
+    return {d.zx, d.zy, d.zz, d.phi, d.w, {d.fs[0], d.fs[1], d.fs[2]}, d.n, reinterpret_cast<uint4*>(base),
             reinterpret_cast<uint4*>(base + w.ty), d.dim == 3 ? reinterpret_cast<uint4*>(base + w.tz) : nullptr};
 }
 

@@ -208,10 +208,14 @@ hipError_t launch_mode_params(const double* z, const double* phi, int dim, int64
                               const double* ell, double* out, hipStream_t s);
 
 // ---------------------------------------------------------------- direct kernels
-// One direct grid sum: the (axis-aligned) mode table, the grid and the outputs (each may be nullptr;
-// y64, k64, mu64 and amp64 are the FP64 form's).
+// One direct or folded grid sum: the (axis-aligned) mode table, the grid and the outputs (each may be
+// nullptr; y64, k64, mu64 and amp64 are the FP64 form's).  A grid one cell wide along x has nothing to
+// fold there: its axes are renamed so that x is the first one with more cells (fold_axis), which
+// leaves every cell where it lies in memory.
 struct DirectGrid {
-    const double* z;    // [dim][n]
+    const double* zx;   // [n] each; zz nullptr in 2-D
+    const double* zy;
+    const double* zz;
     const double* phi;  // [n]
     const double* w;    // [n] or nullptr (all 1)
     double fs[3];       // 1 / (2 pi ell) per axis, 0 for an absent axis
@@ -229,6 +233,8 @@ struct DirectGrid {
     int64_t mslice;     // modes per slice (blockIdx.z)
     double* partial64;  // raw sums [slice][nq nx] of the slices, or nullptr
 };
+// The axis that a folded sum takes for its x (the others follow in turn).
+int fold_axis(const grf_grid* g, int dim);
 DirectGrid direct_grid_args(const grf_modes* m, const grf_grid* g, float* y, float* k, uint8_t* ind);
 hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream_t s);
 
