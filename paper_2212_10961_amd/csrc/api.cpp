@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <vector>
 
 #include "grf_internal.h"
@@ -588,13 +589,15 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
         FoldPair p;
         const DirectGrid d1 = direct_grid_args(&a1, grid, f1, nullptr, nullptr);
         const DirectGrid d2 = direct_grid_args(&a2, grid, f2, nullptr, nullptr);
+        std::optional<TimedScope> timed;  // the contraction, with the pass that adds its slices
         GRF_HIP(launch_fold_pair(d1, d2, ldp, is_bf16(method), tabs,
-                                 static_cast<char*>(tabs) + grid_ws(&a1, grid, method, nullptr).bytes, &p, s));
+                                 static_cast<char*>(tabs) + grid_ws(&a1, grid, method, nullptr).bytes, &p, &timed, s));
         if (p.slices > 1) {
             GRF_HIP(launch_pluri_slices(p.p1, p.p2, p.slices, C, d1.amp, d2.amp, make_pluri(rule, rt), facies, value,
                                         y1, y2, s));
             return GRF_OK;
         }
+        timed.reset();
     } else if (is_sep(method) && !folds(&a1, grid, method) && !folds(&a2, grid, method) &&
                (!is_hilo(method) || padded_modes(a2.n) == ldp)) {  // (other hi+lo pairs run one after the other)
         // both fields: one launch of the six (2-D: four) tables, one of the contraction
@@ -607,6 +610,7 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
         const SepArgs s2 = sep_args(&a2, grid, method, -1, Epi{}, f2, nullptr, nullptr, w2);
         SepArgs s1 = sep_args(&a1, grid, method, -1, Epi{}, f1, nullptr, nullptr, w1);
         s1.timed = true;
+        TimedScope timed(s, s1.partial != nullptr);  // unsplit: stamped on the contraction's dispatch
         GRF_HIP(launch_sep_pair(s1, &s2, s, false));
         if (s1.partial) {
             GRF_HIP(launch_pluri_slices(s1.partial, s2.partial, s1.slices, C, s1.amp, s2.amp, make_pluri(rule, rt),

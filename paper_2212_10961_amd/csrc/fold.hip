@@ -710,7 +710,7 @@ hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi
 }
 
 hipError_t launch_fold_pair(const DirectGrid& d1, const DirectGrid& d2, int64_t ldp, bool bf, void* ws1, void* ws2,
-                            FoldPair* out, hipStream_t s)
+                            FoldPair* out, std::optional<TimedScope>* timed, hipStream_t s)
 {
     const FoldWs w = fold_ws(d1.nx, d1.ny, d1.nq / d1.ny, ldp, d1.dim, true, 2);
     *out = {nullptr, nullptr, w.slices};
@@ -720,7 +720,7 @@ hipError_t launch_fold_pair(const DirectGrid& d1, const DirectGrid& d2, int64_t 
     }
     const hipError_t e = fold_tables(d1, &d2, ldp, bf, w, ws1, ws2, s);
     if (e != hipSuccess) return e;
-    TimedScope scope(s);
+    timed->emplace(s);
     return fold_sums(d1, &d2, ldp, bf, Epi{}, w, ws1, ws2, s);
 }
 

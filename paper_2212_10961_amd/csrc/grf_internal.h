@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <optional>
 #include <string>
 
 #include "grf.h"
@@ -255,14 +256,14 @@ bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t 
 hipError_t launch_fold(const DirectGrid& d, int64_t ldp, bool bf, const Epi& epi, void* ws, bool split, hipStream_t s);
 // Two fields on one grid (tables of one padded length) by one launch of the tables and one of the
 // contraction, each with a workspace of fold_ws; out: the slice sums where the modes are split
-// (slices > 1; the fields are not stored then).
+// (slices > 1; the fields are not stored then); timed: opened before the contraction.
 struct FoldPair {
     float* p1;
     float* p2;
     int slices;
 };
 hipError_t launch_fold_pair(const DirectGrid& d1, const DirectGrid& d2, int64_t ldp, bool bf, void* ws1, void* ws2,
-                            FoldPair* out, hipStream_t s);
+                            FoldPair* out, std::optional<TimedScope>* timed, hipStream_t s);
 // `ws` (ws_doubles FP64 values) holds the sums of the mode slices where the launch takes slices.
 hipError_t launch_direct_grid_f64(const DirectGrid& g, const Epi& epi, double* ws, size_t ws_doubles, hipStream_t s);
 // `partial` (workspace, points_mode_slices(P, n) * P floats when that is > 1) receives the
@@ -349,7 +350,7 @@ struct SepArgs {
 hipError_t launch_sep(const SepArgs& a, hipStream_t s);
 // Two fields on the same grid (same method, sizes and ldp; the epilogue parameters of `a`
 // apply to both) in one launch; b may be nullptr.  add = false leaves the slice sums of a mode
-// split in `partial`.
+// split in `partial`, and the timing of a split to the caller.
 hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s, bool add = true);
 int sep_tile_count();                // number of tile selectors
 void sep_tile_shape(int tile, int* bm, int* bn);

@@ -1216,7 +1216,7 @@ hipError_t launch_sep_pair(const SepArgs& a, const SepArgs* b, hipStream_t s, bo
     if (split && (a.tile >= 0 || a.slices < 1 || a.pairs < 1 || (b && b->partial == nullptr) ||
                   static_cast<int64_t>(a.slices) * a.pairs * 2 * kJC < a.ldp))
         return hipErrorInvalidValue;
-    TimedScope timed(s, split && a.timed);  // the contraction and, if added here, the slice sums
+    TimedScope timed(s, split && add && a.timed);  // the contraction and the slice sums
     hipError_t e;
     switch (a.method) {
     case GRF_SEP_BF16: e = launch_d<true, false>(a, b, tile, s); break;
