@@ -559,9 +559,11 @@ hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream
     const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2;
     auto tiles = [&](int64_t rows, int64_t cols) { return ((half + cols - 1) / cols) * ((g.nq + rows - 1) / rows); };
     // A tile's time does not depend on how many there are until the CUs are full, and grows with
-    // its area: the widest tile that fills most of the 256 CUs.  4,096 modes, us per call for
-    // 64 x 32 / 32 x 32 / 16 x 16: 64^3 (128 tiles of 32 x 32) 91 / 53 / 42; 1024 x 512 (256) 96 / 58
-    // / 78; 128^3 (1,024) 187 / 193 / 262; 3,000 modes on 100 x 90 x 80 (450) 76 / 80 / 109.
+    // its area: the widest tile that fills most of the 256 CUs.  Kernel time in us with 256 / 1,024 /
+    // 4,096 modes for 64 x 32, 32 x 32 and 16 x 16: 64^3 (64 tiles of 64 x 32) 11 / 27 / 91, 7.6 / 17 / 52
+    // and 7.0 / 15 / 41; 1024 x 512 (128) 12 / 28 / 95, 8.2 / 18 / 56 and 10 / 23 / 74; 100 x 90 x 80 (226)
+    // 12 / 29 / 99, 12 / 31 / 104 and 17 / 41 / 142; 128^3 (512) 20 / 54 / 191, 21 / 58 / 204 and 28 / 80 /
+    // 273.
     if (tiles(64, 32) >= 160) return launch_direct_tile<float, 32, 2>(g, epi, s);
     if (tiles(32, 32) >= 192) return launch_direct_tile<float, 32, 1>(g, epi, s);
     return launch_direct_tile<float, 16, 1>(g, epi, s);
@@ -573,15 +575,20 @@ hipError_t launch_direct_grid_f64(const DirectGrid& g0, const Epi& epi, double* 
     g.mslice = g.n;
     g.partial64 = nullptr;
     const int64_t half = (static_cast<int64_t>(g.nx) + 1) / 2, C = g.nq * g.nx;
-    // an operand costs several matrix steps: four row tiles per column operand once they fill the CUs
-    // (five operands for 64 rows; one row tile takes two for 16, fewer up to 32 rows: 65,536 x 1 cells
-    // x 1,000 modes 121 us for 340)
-    if (g.nq > 32 && ((half + 15) / 16) * ((g.nq + 63) / 64) >= 256)
+    // An operand costs several matrix steps: four row tiles per column operand once they fill most CUs.
+    // Kernel time in us, four / one, with 256 and 1,000 modes: 512 x 512 (128 tiles of 64 rows) 19 / 14
+    // and 52 / 38; 700 x 600 (220) 21 / 24 and 53 / 70; 1024 x 512 (256) 21 / 25 and 54 / 72.  (Five
+    // operands for 64 rows, two for 16: one is the better up to 32 rows: 65,536 x 1 cells x 1,000
+    // modes 121 us for 361.)
+    if (g.nq > 32 && ((half + 15) / 16) * ((g.nq + 63) / 64) >= 192)
         return launch_direct_tile<double, 16, 4>(g, epi, s);
-    // few tiles: slices of at least 128 modes spread the operands over more CUs (a second launch
-    // adds the slices in order), where the workspace holds their sums
+    // Few tiles: slices of at least 128 modes spread the operands over more CUs (a second launch adds
+    // the slices in order, about 3 us), where the workspace holds their sums.  64 x 64 (8 tiles),
+    // whole / in slices: 256 modes 7.8 / 8.6 us, 1,000 19 / 9.6, 4,096 63 / 16; 128 x 128 (32) 7.8 / 8.9,
+    // 19 / 11, 64 / 24.
     const int64_t tiles = ((half + 15) / 16) * ((g.nq + 15) / 16);
     int64_t sl = std::min<int64_t>(std::min<int64_t>(128 / tiles, 8), g.n / 128);
+    if (g.n < 384) sl = 1;
     sl = std::min<int64_t>(sl, static_cast<int64_t>(ws_doubles) / C);
     if (sl < 2) return launch_direct_tile<double, 16, 1>(g, epi, s);
     g.mslice = (g.n + sl - 1) / sl;
