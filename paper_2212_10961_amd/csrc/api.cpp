@@ -192,6 +192,12 @@ static bool folds(const grf_modes* m, const grf_grid* g, int method)
                                            m->dim == 3 ? g->n[(a + 2) % 3] : 1, m->n);
 }
 
+static FoldWs grid_fold(const grf_modes* m, const grf_grid* g, int fields)
+{
+    const int d = m->dim, a = fold_axis(g, d);
+    return fold_ws(g->n[a], g->n[(a + 1) % d], d == 3 ? g->n[(a + 2) % 3] : 1, padded_modes(m->n), d, true, fields);
+}
+
 GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
 {
     GridWs w;
@@ -227,8 +233,7 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
     // the folded evaluation keeps its tables, never larger than the ones above (which explicit tiles
     // take), and its slice sums here instead
     if (fold) {
-        const int a = fold_axis(g, dim);
-        const FoldWs f = fold_ws(g->n[a], g->n[(a + 1) % dim], dim == 3 ? g->n[(a + 2) % 3] : 1, ldp, dim, true);
+        const FoldWs f = grid_fold(m, g, 1);
         const size_t tables = c.used;
         c.used = std::max(c.used, f.partial + f.split_bytes);
         w.split_bytes = c.used - tables;
@@ -526,6 +531,15 @@ static int check_pair(const grf_modes* m1, const grf_modes* m2, const char* fn)
     return GRF_OK;
 }
 
+// Tables and sums of one field of the bitruncated grid, alone or in a pair.
+static size_t pluri_field_ws(const grf_modes* m, const grf_grid* g, int method)
+{
+    const size_t b = grid_ws(m, g, method, nullptr).bytes;
+    if (!folds(m, g, method)) return b;
+    const FoldWs f = grid_fold(m, g, 2);
+    return std::max(b, f.partial + f.split_bytes);
+}
+
 // Workspace of the bitruncated grid: the rule's tables, each field the caller does not keep,
 // and the larger of the two fields' table layouts (the two evaluations run one after the other).
 static size_t pluri_grid_ws(const grf_modes* m1, const grf_modes* m2, const grf_grid* g, int method, bool own_y1,
@@ -533,7 +547,7 @@ static size_t pluri_grid_ws(const grf_modes* m1, const grf_modes* m2, const grf_
 {
     const int64_t C = g->n[0] * g->n[1] * g->n[2];
     // separable forms: both fields' tables at once (one table launch, one contraction)
-    const size_t b1 = grid_ws(m1, g, method, nullptr).bytes, b2 = grid_ws(m2, g, method, nullptr).bytes;
+    const size_t b1 = pluri_field_ws(m1, g, method), b2 = pluri_field_ws(m2, g, method);
     const size_t t = is_sep(method) ? b1 + b2 : std::max(b1, b2);
     const size_t f = align256(sizeof(float) * size_t(C));
     return align256(kRuleBytes) + rot_ws_bytes(m1) + rot_ws_bytes(m2) + (own_y1 ? f : 0) + (own_y2 ? f : 0) + t;
@@ -591,7 +605,7 @@ int eval_pluri_grid(const grf_modes* m1, const grf_modes* m2, const grf_grid* gr
         const DirectGrid d2 = direct_grid_args(&a2, grid, f2, nullptr, nullptr);
         std::optional<TimedScope> timed;  // the contraction, with the pass that adds its slices
         GRF_HIP(launch_fold_pair(d1, d2, ldp, is_bf16(method), tabs,
-                                 static_cast<char*>(tabs) + grid_ws(&a1, grid, method, nullptr).bytes, &p, &timed, s));
+                                 static_cast<char*>(tabs) + pluri_field_ws(&a1, grid, method), &p, &timed, s));
         if (p.slices > 1) {
             GRF_HIP(launch_pluri_slices(p.p1, p.p2, p.slices, C, d1.amp, d2.amp, make_pluri(rule, rt), facies, value,
                                         y1, y2, s));

@@ -29,8 +29,8 @@
 // and three pointer tests per cell took 10 us of every block's time (256 x 256 x 64 modes: 16.4 us,
 // 9.1 with the addresses and masks below; 256^3 x 4,096: 422 and 401 in turn on one box).
 // One call, the separable form with the complex product -> this one: 256^3 0.88 -> 0.42 ms;
-// 203 x 171 x 85 x 3,000 modes 0.40 -> 0.087 ms; 128^3 0.17 -> 0.09 ms; 1000 x 500 x 2,048 modes 0.047 ->
-// 0.034 ms, x 64 modes 16 us both (the binding's host work); relative error against FP64 2.2e-6 ->
+// 203 x 171 x 85 x 3,000 modes 0.40 -> 0.087 ms; 128^3 0.17 -> 0.09 ms; 1000 x 500 x 1,024 modes 0.035 ->
+// 0.027 ms, x 64 modes 16 us both (the binding's host work); relative error against FP64 2.2e-6 ->
 // 7.6e-7 on the ragged grid.  (The hardware cosine in the tables would add 10% to the error.)
 #include <hip/hip_runtime.h>
 
@@ -591,12 +591,14 @@ hipError_t launch_tile(const FoldArgs& a0, const Epi& epi, bool bf, int slices, 
 
 bool fold_default(bool bf, int dim, int64_t nx, int64_t ny, int64_t nz, int64_t n)
 {
-    // The bf16 separable form's tables take no software conversion, and a tall 2-D grid gains little
-    // from halved columns: there the complex form is the faster one, below about 6e8 terms.  One call
-    // in us, complex / folded: 256 x 256 x 4,096 modes 26 / 31, 40 x 2000 x 2,048 31 / 36, 16 x 4096
-    // x 512 25 / 29; past the line 100 x 1500 x 4,096 55 / 40, 1024 x 1024 x 1,024 46 / 34, 2000 x
-    // 40 x 4,096 49 / 36.  fp16: 256 x 256 x 4,096 31 / 31, 40 x 2000 x 2,048 41 / 35.
-    return !bf || dim == 3 || nx >= 4 * ny || static_cast<double>(nx * ny * nz) * static_cast<double>(n) >= 6e8;
+    // On a tall 2-D grid the y table takes most of the time, and halved columns gain little: in bf16,
+    // whose separable tables take no software conversion, the complex form is the faster one there
+    // up to about 4e6 table entries and 2e8 terms.  One call in us, complex / folded: 16 x 4096 x 512
+    // modes 24.6 / 29.0, 40 x 2000 x 512, 1,024, 2,048 20.1 / 21.9, 25.3 / 27.8, 31.7 / 36.1, 100 x 1500 x
+    // 1,024 26.2 / 27.6; past the line 40 x 2000 x 4,096 50 / 46, 100 x 1500 x 2,048 39 / 33, 16 x 4096 x
+    // 2,048 54 / 46, 200 x 200 x 4,096 26 / 23.  fp16: 16 x 4096 x 512 32 / 29, 40 x 2000 x 2,048 43 / 36.
+    return !bf || dim == 3 || 8 * nx > ny || ny * n > (int64_t(1) << 22) ||
+           static_cast<double>(nx * ny * nz) * static_cast<double>(n) >= 2e8;
 }
 
 FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool split, int fields)
@@ -606,28 +608,39 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     w.ty = align256(size_t(half) * ldp * 8);
     w.tz = w.ty + align256(size_t(ny) * ldp * 8);
     w.partial = w.tz + align256(size_t(dim == 3 ? nz : 0) * ldp * 8);
-    // 128 rows x 128 columns per block, 64 columns where that covers fewer
-    w.wide = (half + 127) / 128 * 128 == (half + 63) / 64 * 64;
-    const int64_t cols = w.wide ? 128 : 64;
-    const int64_t blocks = fields * ((half + cols - 1) / cols) * ((nq + 127) / 128);
-    // One block per CU at a time (LDS): launches of at most half the 256 CUs may split the modes into
+    // One block per CU at a time (LDS).  Launches of at most half the 256 CUs may split the modes into
     // slices of at least four stages (64 modes) that fill them; the slices' sums take at most 32
-    // MiB.  A stage takes about 0.9 us in a wide block (0.6 in a narrow one), each slice writes and
-    // reads 4 bytes per cell at about 5 TB/s, and the second pass costs 3 us besides: as many
-    // slices as make the sum of these smallest, one where no split pays.  256 x 256 x 64 cells x
-    // 256 modes: 39 us in two slices, 26 in one; 256 x 256 x 2,048: 13 us + 4 for the sums in 16.
+    // MiB.  Blocks are 128 rows x 128 columns (a stage takes about 0.9 us) or x 64 (0.6 us); each
+    // slice writes and reads 4 bytes per cell at about 5 TB/s, and the second pass costs 3 us besides:
+    // the width and as many slices as make the sum of these smallest.  GPU time of a call in us, 128 /
+    // 64 columns: 256 x 256 x 64 modes 12.5 / 9.8, x 2,048 25 / 20; 2048 x 2048 x 1,024 55 (two slices) /
+    // 47; 203 x 171 x 85 x 256 22 / 20, x 3,000 90 (two slices) / 111; 256^3 x 256 46 / 61, x 4,096 452 /
+    // 622; 192^3 x 4,096 358 / 398.  Slices: 256 x 256 x 64 x 256 39 in two, 24 in one.
     constexpr int64_t kCUs = 256, kMaxBytes = int64_t(32) << 20;
     const int64_t quads = ldp / (4 * kFs);  // slices are whole groups of four stages
-    int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads), kMaxBytes / (4 * C)) : 1;
-    if (sl > 1) {
-        const double stages = 4.0 * static_cast<double>(quads) * (w.wide ? 0.9 : 0.6);
+    double best = 0.0;
+    for (const bool wide : {true, false}) {
+        const int64_t cols = wide ? 128 : 64;
+        const int64_t blocks = fields * ((half + cols - 1) / cols) * ((nq + 127) / 128);
+        const double stages = 4.0 * static_cast<double>(quads) * (wide ? 0.9 : 0.6);
         const double sums = 8.0 * static_cast<double>(fields * C) / 5e6;
-        sl = std::min<int64_t>(sl, std::max<int64_t>(1, std::llround(std::sqrt(stages / sums))));
-        const double k = static_cast<double>(sl);
-        if (stages <= stages / k + k * sums + 3.0) sl = 1;
+        int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads), kMaxBytes / (4 * C)) : 1;
+        // (a last round of few blocks costs about half a full one)
+        const double rounds = static_cast<double>(blocks) / kCUs, full = static_cast<double>((blocks + kCUs - 1) / kCUs);
+        double cost = (rounds <= 1.0 ? 1.0 : 0.5 * (rounds + full)) * stages;
+        if (sl > 1) {
+            sl = std::min<int64_t>(sl, std::max<int64_t>(1, std::llround(std::sqrt(stages / sums))));
+            const double in_slices = stages / static_cast<double>(sl) + static_cast<double>(sl) * sums + 3.0;
+            if (in_slices < cost) cost = in_slices;
+            else sl = 1;
+        }
+        if (wide || cost < best) {
+            best = cost;
+            w.wide = wide;
+            sl = std::max<int64_t>(sl, 1);
+            w.per = 4 * ((quads + sl - 1) / sl);
+        }
     }
-    if (sl < 2) sl = 1;
-    w.per = 4 * ((quads + sl - 1) / sl);
     w.slices = static_cast<int>((4 * quads + w.per - 1) / w.per);
     w.split_bytes = w.slices > 1 ? align256(sizeof(float) * size_t(w.slices) * size_t(C)) : 0;
     return w;

@@ -241,8 +241,8 @@ hipError_t launch_direct_grid_f32(const DirectGrid& g, const Epi& epi, hipStream
 
 // ---------------------------------------------------------------- folded split-precision grid sum (fold.hip)
 // Offsets of its tables (columns at 0) and slice sums in the workspace, and its launch plan;
-// `split` = false plans without the slices; `fields` = 2 plans a pair in one launch, whose slice sums
-// are never more than one field's own.
+// `split` = false plans without the slices; `fields` = 2 plans a pair in one launch (offsets and sums of
+// each).
 struct FoldWs {
     size_t ty, tz, partial;
     size_t split_bytes;  // of the slice sums
