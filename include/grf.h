@@ -192,15 +192,16 @@ int eval_field_grid_ws_size(const grf_modes* modes, const grf_grid* grid, int me
  *   y, k              device float[C] or NULL; ind device uint8[C] or NULL (C = cells).
  *                     At least one output must be non-NULL.  epi may be NULL when
  *                     k and ind are NULL.
- *   ws, ws_bytes      device workspace of eval_field_grid_ws_size bytes: the per-axis
- *                     tables (the direct methods form their operands on chip; DIRECT_F64
- *                     keeps the sums of its mode slices there); for the separable methods
- *                     on grids of too few blocks to fill the device's CUs, the FP32 sums of
- *                     the mode slices that the contraction is split into (at most 32 MiB; the slices are added in order by a second pass
- *                     that applies the epilogue).  A workspace smaller than that but large
- *                     enough for the tables runs the contraction unsplit (the same field up
- *                     to FP32 summation order); below that GRF_ENOMEM.  Contents on entry
- *                     are ignored.
+ *   ws, ws_bytes      device workspace of eval_field_grid_ws_size bytes: for the separable methods
+ *                     the per-axis tables and, on grids of too few blocks to fill the device's
+ *                     CUs, the FP32 sums of the mode slices that the contraction is split into (at
+ *                     most 32 MiB; a second pass adds the slices in order and applies the
+ *                     epilogue).  A workspace smaller than that but large enough for the tables
+ *                     runs the contraction unsplit (the same field up to FP32 summation order);
+ *                     below that GRF_ENOMEM.  The direct methods form their operands on chip.
+ *                     The size they ask for is still that of per-axis tables: DIRECT_F64 keeps
+ *                     the sums of its mode slices there, DIRECT_F32 leaves it untouched.
+ *                     Contents on entry are ignored.
  * Separable methods require dim 3 grids with nx, ny >= 1 (any size; ragged tiles
  * are masked) or dim 2 grids.  Phases are range-reduced per axis in FP64.
  */
@@ -214,9 +215,10 @@ int eval_field_grid(const grf_modes* modes, const grf_grid* grid, int method, co
  * GRF_NOALLOC_SCRATCH_BYTES that the library holds on each device it runs on until the
  * process ends, instead of a caller workspace.
  *   Arguments as eval_field_grid without ws / ws_bytes; outputs are still the caller's.
- *   A problem whose tables exceed the scratch size is GRF_ENOMEM, with nothing enqueued;
- *   the separable mode split is taken when its sums fit as well.  Allocates nothing (no hipMalloc, hipFree or
- *   allocating library call); the first call on a device looks up that device's copy.
+ *   A problem whose workspace without slice sums (eval_field_grid) exceeds the scratch size is
+ *   GRF_ENOMEM, with nothing enqueued; the separable mode split is taken when its sums fit as
+ *   well.  Allocates nothing (no hipMalloc, hipFree or allocating library call); the first call
+ *   on a device looks up that device's copy.
  * Every call on one device shares that device's array: calls that overlap on one GPU (other
  * streams or threads, before the previous call's kernels have finished) race on it.  Calls
  * in order on one stream are safe.  The array's contents on entry are never read.

@@ -485,10 +485,12 @@ struct BwdSepK {
 // The dL/dY tiles (hi then lo, 8 KiB each per 32 rows) go through LDS, two buffers, loaded
 // straight from global memory one tile ahead: the four waves share each tile instead of each
 // fetching it from L2, and the fetch overlaps the previous tile's work.
-// Bound by the matrix cores: 128^3 cells x 4096 modes take 193 us, 1.07 PFLOP/s of the 1.25 that a
-// large product reaches here (236 before: a 64-bit division per tile for its slice, and LDS loads
-// that the compiler counted as flat).  With one group the LDS reads of a tile (16 KiB of dL/dY and
-// 8 KiB of Ey per wave) take as long as its 24 MFMAs; two groups share every dL/dY fragment.
+// Bound by the matrix cores and the epilogue's vector work, which share each SIMD: 128^3 cells x 4096
+// modes take 193 us, 1.07 PFLOP/s of the 1.25 that a large product reaches here, matrix cores busy 54%
+// of the cycles at 1.9 GHz with 5.5 other vector instructions for each of theirs (236 us before: a
+// 64-bit division per tile for its slice, and LDS loads that the compiler counted as flat).  With one
+// group the LDS reads of a tile (16 KiB of dL/dY and 8 KiB of Ey per wave) take as long as its 24
+// MFMAs; two groups share every dL/dY fragment.
 typedef __attribute__((address_space(3))) void bwd_lds_void;
 
 // 16 bytes per lane from a uniform base plus an unsigned 32-bit byte offset, in the buffer form

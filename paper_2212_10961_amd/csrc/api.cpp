@@ -205,6 +205,9 @@ GridWs grid_ws(const grf_modes* m, const grf_grid* g, int method, void* base)
     Carve c(base);
     const int64_t ldp = padded_modes(m->n);
     const int dim = m->dim;
+    // The direct sums have no tables.  The bytes they ask for (and refuse to run below) are still
+    // those of FP32 or FP64 revolutions per axis: callers size their buffers by them, DIRECT_F64
+    // keeps its slice sums there, and the direct adjoint's FP32 tables have this layout.
     if (method == GRF_DIRECT_F32) {
         for (int a = 0; a < 3; ++a) w.t[a] = c.take<float>(size_t(g->n[a]) * ldp);
     } else if (method == GRF_DIRECT_F64) {
@@ -540,8 +543,8 @@ static size_t pluri_field_ws(const grf_modes* m, const grf_grid* g, int method)
     return std::max(b, f.partial + f.split_bytes);
 }
 
-// Workspace of the bitruncated grid: the rule's tables, each field the caller does not keep,
-// and the larger of the two fields' table layouts (the two evaluations run one after the other).
+// Workspace of the bitruncated grid: the rule's tables, each field the caller does not keep, and both
+// fields' tables and sums (direct methods, one field after the other: the larger of the two).
 static size_t pluri_grid_ws(const grf_modes* m1, const grf_modes* m2, const grf_grid* g, int method, bool own_y1,
                             bool own_y2)
 {

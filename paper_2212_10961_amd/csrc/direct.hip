@@ -44,12 +44,13 @@ __device__ __forceinline__ void store_out(int64_t c, float yv, const Epi& e, flo
 //
 // What bounds it: 2 flops per mode and cell on the FP32 matrix cores (153 TFLOP/s in a library
 // product) plus the operands, about 41 issue cycles per cosine-sine pair: on gfx950 a vector
-// instruction does not issue beside another wave's FP32 matrix step (measured: the two add up),
-// so a 64-row tile's step of 4 x 64 matrix cycles costs ~380.  Making four steps' operands
-// together changed nothing.  The plain angle sum on the vector units (two FMAs per term on
-// tabulated phases) took, before -> after, one call: 128^3 x 4,096 modes 566 -> 174 us, a weighted
-// 517 x 301 x 2,048 table 120 -> 23 us, 64 x 64 x 1,000 27 -> 13 us; relative error against FP64
-// on 128^3 1.6e-6 -> 4.5e-7 (the phases are summed in FP64 and the chunks are shorter).
+// instruction does not issue beside another wave's FP32 matrix step (128^3 x 4,096 modes: matrix cores
+// busy 60% of the cycles, none of them with vector work), so a 64-row tile's step of 4 x 64 matrix
+// cycles costs ~380.  Making four steps' operands together changed nothing.  The plain angle sum on
+// the vector units (two FMAs per term on tabulated phases) took, before -> after, one call: 128^3 x
+// 4,096 modes 566 -> 175 us, a weighted 517 x 301 x 2,048 table 120 -> 23 us, 64 x 64 x 1,000 27 -> 13 us;
+// relative error against FP64 on 128^3 1.6e-6 -> 4.5e-7 (the phases are summed in FP64 and the chunks
+// are shorter).
 //
 // DIRECT_F64 is the same tile on FP64 operands (sincospi of the FP64 fraction) and the FP64 matrix
 // cores; its operands, not the products, take the time, so larger grids share each column

@@ -21,13 +21,15 @@
 // of between them, and the matrix waves, whose next fragments are always ready, read half a
 // stage ahead.
 //
-// What bounds it: 256^3 x 4,096 modes take 0.36-0.40 ms in k_fold (as the clock allows); without the
-// row products' vector work the matrix cores are busy 73% of the cycles at the 1.6 GHz that the chip
-// holds under this load (1.2 PFLOP/s, the rate of a large library product).  One barrier for
-// all eight waves after loading, splitting and multiplying in turn (no roles) ran at 0.60 ms.
-// With few modes the stores bound it: four waves write 32,768 cells, and a 64-bit index, bounds
-// and three pointer tests per cell took 10 us of every block's time (256 x 256 x 64 modes: 16.4 us,
-// 9.1 with the addresses and masks below; 256^3 x 4,096: 422 and 401 in turn on one box).
+// What bounds it: 256^3 x 4,096 modes take 0.36-0.44 ms in k_fold, box to box and as the chip warms.  By
+// the counters the matrix cores are busy 53% of the cycles, at the 1.86 GHz that the chip holds, and
+// a third of that beside vector work, 3.1 instructions for each of their own; no bank conflicts.
+// One barrier for all eight waves after loading, splitting and multiplying in turn (no roles) ran at
+// 0.60 ms.
+// With few modes the stores bound it: four waves write 32,768 cells, and a 64-bit index, bounds and
+// three pointer tests per cell took 7 us of every block's time (256 x 256 x 64 modes: 16.4 us, 9.1
+// with the addresses and masks below, 6.3 in narrow blocks; 256^3 x 4,096: 422 and 401 in turn on one
+// box).
 // One call, the separable form with the complex product -> this one: 256^3 0.88 -> 0.42 ms;
 // 203 x 171 x 85 x 3,000 modes 0.40 -> 0.087 ms; 128^3 0.17 -> 0.09 ms; 1000 x 500 x 1,024 modes 0.035 ->
 // 0.027 ms, x 64 modes 16 us both (the binding's host work); relative error against FP64 2.2e-6 ->
