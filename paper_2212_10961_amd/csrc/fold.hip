@@ -536,6 +536,15 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
         __builtin_amdgcn_sched_group_barrier(0x008, NM - NR > 0 ? NM - NR : 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
+    // What the stores need, held in registers from here: loads of the arguments after the last stage
+    // would each wait for memory.
+    const bool raw = f.partial != nullptr;
+    float* y = raw ? f.partial + slice * (a.nq * a.nx) : f.y;
+    float* kk = raw ? nullptr : a.k;
+    uint8_t* ind = raw ? nullptr : a.ind;
+    float amp = raw ? 1.f : f.amp;
+    int64_t nx = a.nx;
+    asm volatile("" : "+s"(y), "+s"(kk), "+s"(ind), "+v"(amp), "+s"(nx));
     Frag f0, f1;
     bare_barrier();
     read(0, 0, f0);
@@ -556,11 +565,6 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
     // Output addresses: a uniform 64-bit row base and two 32-bit lane offsets per tile (a cell and its
     // mirror, at most 4 rows of 2^24 cells on), rows past the grid masked by one compare.  (The
     // middle cell of an odd row is its own mirror: B = 0 and O = 0 there, the same value twice.)
-    const bool raw = f.partial != nullptr;
-    float* const y = raw ? f.partial + slice * (a.nq * a.nx) : f.y;
-    float* const kk = raw ? nullptr : a.k;
-    uint8_t* const ind = raw ? nullptr : a.ind;
-    const float amp = raw ? 1.f : f.amp;
     auto store = [&](auto put) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -570,30 +574,32 @@ __global__ __launch_bounds__(512, 2) void k_fold(FoldArgs a, Epi epi)
             for (int j = 0; j < TN; ++j) {
                 const int64_t col = i0 + (wn * TN + j) * 32 + lr;
                 const int lim = col < a.half ? rows - 4 * h : 0;
-                const uint32_t c0 = static_cast<uint32_t>(4 * h * a.nx + col);
-                const uint32_t c1 = static_cast<uint32_t>(4 * h * a.nx + (a.nx - 1 - col));
+                const uint32_t c0 = static_cast<uint32_t>(4 * h * nx + col);
+                const uint32_t c1 = static_cast<uint32_t>(4 * h * nx + (nx - 1 - col));
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int r = 8 * (e >> 2) + (e & 3);
                     if (r >= lim) continue;
                     const float ev = ae[i][j][e], ov = ao[i][j][e];
-                    put((qt + r) * a.nx, c0, amp * (ev - ov));
-                    put((qt + r) * a.nx, c1, amp * (ev + ov));
+                    put((qt + r) * nx, c0, amp * (ev - ov));
+                    put((qt + r) * nx, c1, amp * (ev + ov));
                 }
             }
         }
     };
-    if (!kk && !ind)
-        store([&](int64_t row, uint32_t c, float v) { global_ptr(y + row)[c] = v; });
-    else
+    // One pass per output: pointer tests and the facies loop at each cell would cost as much as the stores
+    // (192^3 x 200 modes, K alone: 61 us so, 46 now; Y and K 62, 54).
+    if (y) store([&](int64_t row, uint32_t c, float v) { global_ptr(y + row)[c] = v; });
+    if (kk)
         store([&](int64_t row, uint32_t c, float v) {
-            if (y) global_ptr(y + row)[c] = v;
-            if (kk) global_ptr(kk + row)[c] = expf(epi.mu + v);
-            if (ind) {
-                int facies = 0;
-                for (int t = 0; t < epi.nthr; ++t) facies += v > epi.thr[t] ? 1 : 0;
-                global_ptr(ind + row)[c] = static_cast<uint8_t>(facies);
-            }
+#pragma clang fp contract(off)  // Y rounded before mu is added, as in the per-cell path
+            global_ptr(kk + row)[c] = expf(epi.mu + v);
+        });
+    if (ind)
+        store([&](int64_t row, uint32_t c, float v) {
+            int facies = 0;
+            for (int t = 0; t < epi.nthr; ++t) facies += v > epi.thr[t] ? 1 : 0;
+            global_ptr(ind + row)[c] = static_cast<uint8_t>(facies);
         });
 }
 
