@@ -645,37 +645,37 @@ FoldWs fold_ws(int64_t nx, int64_t ny, int64_t nz, int64_t ldp, int dim, bool sp
     w.ty = align256(size_t(half) * ldp * 8);
     w.tz = w.ty + align256(size_t(ny) * ldp * 8);
     w.partial = w.tz + align256(size_t(dim == 3 ? nz : 0) * ldp * 8);
-    // One block per CU at a time (LDS).  Launches of at most half the 256 CUs may split the modes into
-    // slices of at least four stages (64 modes) that fill them; the slices' sums take at most 32
-    // MiB.  Blocks are 128 rows x 128 columns (a stage takes about 0.9 us) or x 64 (0.6 us); each
-    // slice writes and reads 4 bytes per cell at about 5 TB/s, and the second pass costs 3 us besides:
-    // the width and as many slices as make the sum of these smallest.  GPU time of a call in us, 128 /
-    // 64 columns: 256 x 256 x 64 modes 12.5 / 9.8, x 2,048 25 / 20; 2048 x 2048 x 1,024 55 (two slices) /
-    // 47; 203 x 171 x 85 x 256 22 / 20, x 3,000 90 (two slices) / 111; 256^3 x 256 46 / 61, x 4,096 452 /
-    // 622; 192^3 x 4,096 358 / 398.  Slices: 256 x 256 x 64 x 256 39 in two, 24 in one.
+    // One block per CU at a time (LDS), so the blocks run in rounds of 256: 128 rows x 128 columns (2.3 us
+    // per four stages, 9.5 us besides, K's exponentials 6 more) or x 64 (1.9, 7, 3).  Launches of at
+    // most half the CUs may split the modes into slices of whole groups of four stages (64 modes); the
+    // slices' sums take at most 32 MiB, each slice writes and reads 4 bytes per cell at about 4 TB/s,
+    // and the second pass costs 3 us besides but hides K's exponentials.  The width and as many slices as
+    // make the sum of these smallest, half of K's part counted.  GPU time of a call in us, 128 / 64 columns:
+    // 256 x 256 x 64 x 64 modes 17 / 15, x 256 24 / 21, x 2,048 78 (two slices) / 89; 2048 x 2048 x 1,024 56
+    // (two slices) / 49; 203 x 171 x 85 x 256 23 / 20, x 3,000 93 (two slices) / 113; 192^3 x 200 40 / 44, x
+    // 4,096 348 / 408; 256^3 x 256 47 / 63, x 4,096 435 / 622.  Slices: 256 x 256 x 64 x 256 39 in two, 24
+    // in one; 1500 x 1200 x 475 32 in two, 26 in one.
     constexpr int64_t kCUs = 256, kMaxBytes = int64_t(32) << 20;
-    const int64_t quads = ldp / (4 * kFs);  // slices are whole groups of four stages
-    double best = 0.0;
+    const int64_t quads = ldp / (4 * kFs);
+    double best = -1.0;
     for (const bool wide : {true, false}) {
         const int64_t cols = wide ? 128 : 64;
         const int64_t blocks = fields * ((half + cols - 1) / cols) * ((nq + 127) / 128);
-        const double stages = 4.0 * static_cast<double>(quads) * (wide ? 0.9 : 0.6);
-        const double sums = 8.0 * static_cast<double>(fields * C) / 5e6;
-        int64_t sl = split ? std::min<int64_t>(std::min<int64_t>(kCUs / blocks, quads), kMaxBytes / (4 * C)) : 1;
-        // (a last round of few blocks costs about half a full one)
-        const double rounds = static_cast<double>(blocks) / kCUs, full = static_cast<double>((blocks + kCUs - 1) / kCUs);
-        double cost = (rounds <= 1.0 ? 1.0 : 0.5 * (rounds + full)) * stages;
-        if (sl > 1) {
-            sl = std::min<int64_t>(sl, std::max<int64_t>(1, std::llround(std::sqrt(stages / sums))));
-            const double in_slices = stages / static_cast<double>(sl) + static_cast<double>(sl) * sums + 3.0;
-            if (in_slices < cost) cost = in_slices;
-            else sl = 1;
-        }
-        if (wide || cost < best) {
+        const double stage4 = wide ? 2.32 : 1.88, rest = wide ? 9.5 : 7.0, k = wide ? 3.0 : 1.5;
+        const double sums = 8.0 * static_cast<double>(fields * C) / 4e6;
+        auto take = [&](int64_t per, double cost) {
+            if (best >= 0.0 && cost >= best) return;
             best = cost;
             w.wide = wide;
-            sl = std::max<int64_t>(sl, 1);
-            w.per = 4 * ((quads + sl - 1) / sl);
+            w.per = 4 * per;
+        };
+        take(quads, static_cast<double>((blocks + kCUs - 1) / kCUs) * (static_cast<double>(quads) * stage4 + rest + k));
+        const int64_t most = split ? std::min<int64_t>(kCUs / blocks, kMaxBytes / (4 * C)) : 1;
+        if (most < 2) continue;
+        const auto near = static_cast<int64_t>(std::sqrt(static_cast<double>(quads) * sums / stage4));
+        for (int64_t per = std::max(near, (quads + most - 1) / most), i = 0; i < 2; ++per, ++i) {
+            const int64_t sl = (quads + per - 1) / per;
+            if (sl > 1) take(per, static_cast<double>(per) * stage4 + rest + static_cast<double>(sl) * sums + 3.0);
         }
     }
     w.slices = static_cast<int>((4 * quads + w.per - 1) / w.per);
